@@ -66,6 +66,10 @@ def build_library(verbose=False, jobs=8, force=True):
     source or any header) and link liblfft.so."""
     os.makedirs(BUILD, exist_ok=True)
     srcs = sources()
+    keep = {os.path.basename(s) + ".o" for s in srcs}
+    for f in os.listdir(BUILD):   # objects of sources that are gone
+        if f.endswith(".o") and f not in keep:
+            os.remove(os.path.join(BUILD, f))
     with cf.ThreadPoolExecutor(max_workers=min(jobs, len(srcs))) as ex:
         objs = list(ex.map(lambda s: _compile(s, force), srcs))
     tmp = LIB + ".tmp"

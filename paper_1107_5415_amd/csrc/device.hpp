@@ -9,6 +9,19 @@ namespace lfft {
 
 constexpr int kMaxStages = 24;
 
+// floor(n / d) for 0 <= n < 2^31 as (n * mag) >> (31 + sh), with
+// sh = ceil(log2 d) and mag = floor(2^(31 + sh) / d) + 1 < 2^32 (division by
+// an invariant integer through multiplication; the rounding error of the
+// scaled reciprocal stays below 1/d for n < 2^31).
+struct FastDiv {
+  unsigned mag;
+  int sh;
+};
+
+__host__ __device__ __forceinline__ unsigned fast_div(unsigned n, FastDiv f) {
+  return (unsigned)(((unsigned long long)n * f.mag) >> (31 + f.sh));
+}
+
 // How a pass addresses the buffer on one side.
 //   IDENTITY : the internal grid layout, index = ((b*O + o)*L + l)*S + s
 //   LINEAR   : separable offsets, index = b*bstride + To[o].x + Tl[l].x + Ts[s].x
@@ -20,6 +33,8 @@ enum MapMode : int { MAP_IDENTITY = 0, MAP_LINEAR = 1, MAP_NATURAL = 2 };
 struct MapDesc {
   int mode;
   int d;
+  int across;                 // mixed-radix kernel: neighbouring threads on neighbouring
+                              // pencils (0: on neighbouring positions of one pencil)
   int H[4][4];
   long long box_stride[4];
   long long bstride;          // batch stride in elements (LINEAR / NATURAL)
@@ -39,17 +54,26 @@ struct StageDesc {
   const float2* tw;
   // base-2 logarithms (power-of-two stages only, used by the fast kernel)
   int lg_r, lg_n, lg_stride, lg_Ns;
+  // mixed-radix kernel: divisions by the stride, by n / radix, by Ns and by
+  // the butterflies of one pencil, L / radix
+  FastDiv f_stride, f_nr, f_Ns, f_per;
 };
 
 struct PassDesc {
-  int kind;                   // 0 generic, 1 register-resident power-of-two, 2 streaming,
+  int kind;                   // 0 mixed-radix, 1 register-resident power-of-two, 2 streaming,
                               // 3 split-BF16 MFMA, 4 chirp-z (one whole axis)
   int P;                      // fast kernel: points per thread (16 or 32)
   int W;                      // fast kernel: pencils per workgroup
   int split;                  // fast kernel: exchange real and imaginary parts separately
   long long batch;            // number of signals
   int O, L, S;                // per-signal outer count, pencil length, inner count
-  int TP;                     // pencils per tile
+  // mixed-radix kernel: pencils per tile, threads, the LDS position of pencil
+  // position l of tile pencil w (l * ls + w * ws), 64-bit coordinates, and
+  // its divisions
+  int TP, NT;
+  int ls, ws;
+  int wide;
+  FastDiv f_TP, f_S, f_OS, f_L, f_lmod, f_lodiv, f_lon;
   int nst;
   StageDesc st[kMaxStages];
   int sign;                   // -1 forward, +1 inverse
@@ -103,19 +127,6 @@ enum BatchVariant : int {
   BATCH_ROWS_IN = 3,          // contiguous pencils, grid in, natural out
   BATCH_COLS_IN = 4,          // strided pencils, grid in, natural out
 };
-
-// floor(n / d) for 0 <= n < 2^31 as (n * mag) >> (31 + sh), with
-// sh = ceil(log2 d) and mag = floor(2^(31 + sh) / d) + 1 < 2^32 (division by
-// an invariant integer through multiplication; the rounding error of the
-// scaled reciprocal stays below 1/d for n < 2^31).
-struct FastDiv {
-  unsigned mag;
-  int sh;
-};
-
-__host__ __device__ __forceinline__ unsigned fast_div(unsigned n, FastDiv f) {
-  return (unsigned)(((unsigned long long)n * f.mag) >> (31 + f.sh));
-}
 
 // One level of the Fourier-domain wavelet split (natural orders).
 struct SplitDesc {

@@ -1,0 +1,152 @@
+// In-register DFTs of any small length: odd primes by the symmetric sum over
+// x_j + x_{p-j} and x_j - x_{p-j}, composites as a product of two shorter
+// ones.  The roots of unity are compile-time constants, evaluated in FP64 and
+// rounded once.
+#pragma once
+#include "fft_common.hpp"
+
+namespace lfft {
+namespace dev {
+
+constexpr double kTwoPi = 6.283185307179586476925286766559;
+
+// Taylor series on |x| <= pi/4
+constexpr double sin_small(double x) {
+  double t = x, s = x;
+  for (int k = 1; k < 12; ++k) {
+    t *= -x * x / ((2 * k) * (2 * k + 1));
+    s += t;
+  }
+  return s;
+}
+constexpr double cos_small(double x) {
+  double t = 1, s = 1;
+  for (int k = 1; k < 12; ++k) {
+    t *= -x * x / ((2 * k - 1) * (2 * k));
+    s += t;
+  }
+  return s;
+}
+// cos and sin of 2 pi k / n, the angle reduced to an octant in integers
+constexpr double cos_frac(int k, int n) {
+  k %= n;
+  if (2 * k > n) k = n - k;                     // [0, pi]
+  if (4 * k > n) return -cos_frac(n - 2 * k, 2 * n);  // pi - x
+  if (8 * k > n) return sin_small(kTwoPi * (n - 4 * k) / (4.0 * n));
+  return cos_small(kTwoPi * k / n);
+}
+constexpr double sin_frac(int k, int n) {
+  k %= n;
+  if (2 * k > n) return -sin_frac(n - k, n);
+  if (4 * k > n) return sin_frac(n - 2 * k, 2 * n);
+  if (8 * k > n) return cos_small(kTwoPi * (n - 4 * k) / (4.0 * n));
+  return sin_small(kTwoPi * k / n);
+}
+
+template <int N>
+struct Roots {
+  float c[N] = {}, s[N] = {};
+  constexpr Roots() {
+    for (int k = 0; k < N; ++k) {
+      c[k] = (float)cos_frac(k, N);
+      s[k] = (float)sin_frac(k, N);
+    }
+  }
+};
+
+// f(k, X_k) for every output k of the DFT of odd length P, in pairs
+// (k, P - k): with a = x_0 + sum_j cos(2 pi jk/P) (x_j + x_{P-j}) and
+// b = sum_j sin(2 pi jk/P) (x_j - x_{P-j}), X_k = a + sign i b and
+// X_{P-k} = a - sign i b.
+template <int P, class F>
+__device__ __forceinline__ void dft_odd_emit(const float2* v, int sign, F&& f) {
+  constexpr Roots<P> w;
+  constexpr int h = (P - 1) / 2;
+  float2 s[h], d[h];
+  float2 x0 = v[0];
+#pragma unroll
+  for (int j = 1; j <= h; ++j) {
+    s[j - 1] = c_add(v[j], v[P - j]);
+    d[j - 1] = c_sub(v[j], v[P - j]);
+    x0 = c_add(x0, s[j - 1]);
+  }
+  const float2 y0 = v[0];
+  f(0, x0);
+#pragma unroll
+  for (int k = 1; k <= h; ++k) {
+    float2 a = y0, b = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int j = 1; j <= h; ++j) {
+      const float c = w.c[(j * k) % P], q = w.s[(j * k) % P];
+      a.x += c * s[j - 1].x;
+      a.y += c * s[j - 1].y;
+      b.x += q * d[j - 1].x;
+      b.y += q * d[j - 1].y;
+    }
+    b = c_muli(b, sign);
+    f(k, c_add(a, b));
+    f(P - k, c_sub(a, b));
+  }
+}
+
+// v <- DFT of length R, exponent sign `sign`
+template <int R>
+__device__ __forceinline__ void dft_small(float2* v, int sign);
+
+// R = A B: DFTs of length A over the inputs of step B, the twiddles
+// exp(sign 2 pi i k1 i2 / R), then DFTs of length B; output k1 + A k2.
+template <int A, int B>
+__device__ __forceinline__ void dft_two(float2* v, int sign) {
+  constexpr Roots<A * B> w;
+  float2 t[B][A];
+#pragma unroll
+  for (int i2 = 0; i2 < B; ++i2) {
+#pragma unroll
+    for (int i1 = 0; i1 < A; ++i1) t[i2][i1] = v[B * i1 + i2];
+    dft_small<A>(t[i2], sign);
+#pragma unroll
+    for (int k1 = 1; k1 < A; ++k1)
+      if (i2 > 0) {
+        const float c = w.c[(i2 * k1) % (A * B)], q = w.s[(i2 * k1) % (A * B)];
+        t[i2][k1] = c_mul(t[i2][k1], make_float2(c, sign < 0 ? -q : q));
+      }
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < A; ++k1) {
+    float2 u[B];
+#pragma unroll
+    for (int i2 = 0; i2 < B; ++i2) u[i2] = t[i2][k1];
+    dft_small<B>(u, sign);
+#pragma unroll
+    for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = u[k2];
+  }
+}
+
+template <int R>
+__device__ __forceinline__ void dft_small(float2* v, int sign) {
+  if constexpr ((R & (R - 1)) == 0) {
+    dft_pow2<R>(v, sign);
+  } else if constexpr (R == 3) {
+    dft3(v, sign);
+  } else if constexpr (R == 6) {
+    dft_two<2, 3>(v, sign);
+  } else if constexpr (R == 9) {
+    dft_two<3, 3>(v, sign);
+  } else if constexpr (R == 10) {
+    dft_two<2, 5>(v, sign);
+  } else if constexpr (R == 12) {
+    dft_two<4, 3>(v, sign);
+  } else if constexpr (R == 14) {
+    dft_two<2, 7>(v, sign);
+  } else if constexpr (R == 15) {
+    dft_two<3, 5>(v, sign);
+  } else {
+    float2 y[R];
+    dft_odd_emit<R>(v, sign, [&](int k, float2 x) { y[k] = x; });
+#pragma unroll
+    for (int k = 0; k < R; ++k) v[k] = y[k];
+  }
+}
+
+}  // namespace dev
+}  // namespace lfft

@@ -134,21 +134,31 @@ __device__ __forceinline__ void dft3(float2* v, int sign) {
   v[2] = c_sub(mm, nn);
 }
 
-struct Coords {
-  long long c[4];
-};
-
+// c += b in Z^d / H Z^d for reduced c and b in 64 bits (lattices of 2^30
+// points and more): coordinate i needs at most 4 - i subtractions of column i
+// and 3 - i additions, as in gadd32 below.  Unrolled so that c stays in
+// registers; the columns beyond d are never used.
 __device__ __forceinline__ void group_add(const MapDesc& m, long long* c, int4 b) {
   c[0] += b.x;
   c[1] += b.y;
   c[2] += b.z;
   c[3] += b.w;
-  for (int i = m.d - 1; i >= 0; --i) {
-    const long long hii = m.H[i][i];
-    while (c[i] >= hii)
-      for (int r = 0; r <= i; ++r) c[r] -= m.H[r][i];
-    while (c[i] < 0)
-      for (int r = 0; r <= i; ++r) c[r] += m.H[r][i];
+#pragma unroll
+  for (int i = 3; i >= 0; --i) {
+    if (i < m.d) {
+#pragma unroll
+      for (int t = 0; t < 4 - i; ++t) {
+        const bool over = c[i] >= m.H[i][i];
+#pragma unroll
+        for (int r = 0; r <= i; ++r) c[r] -= over ? m.H[r][i] : 0;
+      }
+#pragma unroll
+      for (int t = 0; t < 3 - i; ++t) {
+        const bool under = c[i] < 0;
+#pragma unroll
+        for (int r = 0; r <= i; ++r) c[r] += under ? m.H[r][i] : 0;
+      }
+    }
   }
 }
 
@@ -162,10 +172,10 @@ __device__ __forceinline__ long long map_index(const MapDesc& m, long long b, in
   group_add(m, c, m.Tl[l]);
   group_add(m, c, m.Ts[s]);
   long long idx = b * m.bstride;
-  for (int i = 0; i < m.d; ++i) idx += c[i] * m.box_stride[i];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) idx += c[i] * m.box_stride[i];
   return idx;
 }
-
 
 }  // namespace dev
 }  // namespace lfft

@@ -1,0 +1,443 @@
+// Mixed-radix FFT pass for gfx950: any pencil length up to 8192.  One
+// workgroup owns a tile of TP pencils that moves between two LDS buffers, one
+// Stockham stage per move; radices 2 .. 16 and the primes 17 .. 31 run in
+// registers, larger primes (only inside pencils of several digits, see
+// chirp_tile.hip for the others) as a sum shared by all threads.
+//
+// The first stage reads its butterflies straight from the input order and the
+// last one writes straight to the output order, through the planner's maps
+// (Section 3 bases, Theorem 1 of Section 4.1): the R positions of a butterfly
+// are an arithmetic progression in one digit, so their natural coordinates
+// follow by repeated group addition of one constant, and neither order is
+// ever materialised.  Neighbouring threads take neighbouring pencils or
+// neighbouring positions, chosen per side by the planner for the shorter
+// memory step.
+//
+// Bound by latency and by the vector ALUs, not by HBM: a stage is one LDS
+// round trip and a barrier, so stages are few and wide, and tiles are small
+// enough (4096 elements, 70 KB for both buffers) for two workgroups of eight
+// waves per CU.  All index splits are multiplications by precomputed
+// reciprocals: with the integer divisions (64-bit for every twiddle) of a
+// direct formulation, and single threads summing a prime's inputs, 1088
+// points (8 x 17) took 111 us and 8 x 135135 points 494 us.
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+
+#include "dft_small.hpp"
+#include "kernels.hpp"
+
+namespace lfft {
+namespace {
+using namespace dev;
+
+constexpr int kPassThreads = 1024;
+
+// The descriptor through the kernel argument segment (scalar loads).  Each
+// stage takes a fresh view of it: the compiler would otherwise hoist every
+// field that any radix reads to the kernel's entry and spill them.
+typedef const __attribute__((address_space(4))) PassDesc* PassArg;
+__device__ __forceinline__ const PassDesc& fresh(PassArg k) {
+  asm volatile("" : "+s"(k));
+  return *(const PassDesc*)k;
+}
+
+// a table pointer read from the descriptor points to device memory
+template <class T>
+__device__ __forceinline__ const T* dev_ptr(const T* x) {
+  return (const T*)(const __attribute__((address_space(1))) T*)x;
+}
+
+__device__ __forceinline__ int mphys(int e) { return e + (e >> 4); }
+
+struct Tile {
+  long long b0;    // signal of the tile's first pencil
+  int r0;          // its index o S + s inside the signal
+  int n;           // pencils of this tile
+};
+
+struct Pencil {
+  long long b;
+  int o, s;
+};
+
+__device__ __forceinline__ Pencil pencil_of(const PassDesc& p, const Tile& t, int w) {
+  const unsigned r = (unsigned)(t.r0 + w);
+  const unsigned q = fast_div(r, p.f_OS);
+  const unsigned i = r - q * (unsigned)(p.O * p.S);
+  Pencil c;
+  c.b = t.b0 + q;
+  c.o = (int)fast_div(i, p.f_S);
+  c.s = (int)(i - (unsigned)c.o * (unsigned)p.S);
+  return c;
+}
+
+// Element offsets (below 2^31) inside the signal of positions l0 + i step,
+// i < R, of one pencil; the positions differ in one digit only.
+template <int R, bool WIDE>
+__device__ __forceinline__ void offsets(const PassDesc& p, const MapDesc& m, const Pencil& c, int l0,
+                                        int step, unsigned* off) {
+  if (m.mode == MAP_IDENTITY) {
+    const unsigned a = ((unsigned)c.o * (unsigned)p.L + (unsigned)l0) * (unsigned)p.S + (unsigned)c.s;
+#pragma unroll
+    for (int i = 0; i < R; ++i) off[i] = a + (unsigned)(i * step) * (unsigned)p.S;
+  } else if (m.mode == MAP_LINEAR) {
+    const int4* Tl = dev_ptr(m.Tl);
+    const unsigned a = (unsigned)(dev_ptr(m.To)[c.o].x + dev_ptr(m.Ts)[c.s].x) + (unsigned)Tl[l0].x;
+    const unsigned d = R > 1 ? (unsigned)Tl[step].x : 0u;
+#pragma unroll
+    for (int i = 0; i < R; ++i) off[i] = a + (unsigned)i * d;
+  } else {
+    const int4 To = dev_ptr(m.To)[c.o], Ts = dev_ptr(m.Ts)[c.s], Tl = dev_ptr(m.Tl)[l0];
+    const int4 D = R > 1 ? dev_ptr(m.Tl)[step] : make_int4(0, 0, 0, 0);
+    if constexpr (WIDE) {
+      // coordinates past 2^30: 64-bit sums
+      long long x[4] = {0, 0, 0, 0};
+      group_add(m, x, To);
+      group_add(m, x, Ts);
+      group_add(m, x, Tl);
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        long long k = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) k += x[j] * m.box_stride[j];
+        off[i] = (unsigned)k;
+        if (i + 1 < R) group_add(m, x, D);
+      }
+    } else if (m.d == 2) {
+      int c0 = To.x, c1 = To.y;
+      gadd2(m, c0, c1, Ts);
+      gadd2(m, c0, c1, Tl);
+      const int h11 = m.H[1][1];
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        off[i] = (unsigned)(c0 * h11 + c1);
+        if (i + 1 < R) gadd2(m, c0, c1, D);
+      }
+    } else if (m.d == 3) {
+      int x[4] = {To.x, To.y, To.z, 0};
+      gadd3(m, x, Ts);
+      gadd3(m, x, Tl);
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        off[i] = (unsigned)nat_index3(m, x);
+        if (i + 1 < R) gadd3(m, x, D);
+      }
+    } else {
+      int x[4] = {To.x, To.y, To.z, To.w};
+      gadd32(m, x, Ts);
+      gadd32(m, x, Tl);
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        off[i] = (unsigned)nat_index_i(m, x);
+        if (i + 1 < R) gadd32(m, x, D);
+      }
+    }
+  }
+}
+
+// four-step twiddle exp(sign 2 pi i k lo / postN): k < post_lmod and
+// lo < lo_n, so the product stays below postN = post_lmod lo_n
+__device__ __forceinline__ float2 post_twiddle(const PassDesc& p, unsigned x) {
+  float2 w = c_mul(dev_ptr(p.tw_hi)[x >> 12], dev_ptr(p.tw_lo)[x & 4095]);
+  if (p.sign > 0) w.y = -w.y;
+  return w;
+}
+
+__device__ __forceinline__ unsigned post_lo(const PassDesc& p, int s) {
+  const unsigned q = fast_div((unsigned)s, p.f_lodiv);
+  return q - fast_div(q, p.f_lon) * (unsigned)p.lo_n;
+}
+
+// position of l in the pencil's last digit
+__device__ __forceinline__ unsigned post_pos(const PassDesc& p, unsigned l) {
+  return l - fast_div(l, p.f_lmod) * (unsigned)p.post_lmod;
+}
+
+// Butterfly index -> tile pencil and pencil-local butterfly, with
+// neighbouring indices across the pencils or along one.
+__device__ __forceinline__ void split_bf(const PassDesc& p, FastDiv per, int nper, bool across,
+                                         unsigned bf, int& w, unsigned& q) {
+  if (across) {
+    const unsigned t = fast_div(bf, p.f_TP);
+    w = (int)(bf - t * (unsigned)p.TP);
+    q = t;
+  } else {
+    w = (int)fast_div(bf, per);
+    q = bf - (unsigned)w * (unsigned)nper;
+  }
+}
+
+// multiply input i by w^i, the powers built from w^(2^k) with at most
+// log2(R) products each (primes above 16: every power from the table)
+constexpr int high_bit(int i) { return i < 2 ? i : 2 * high_bit(i / 2); }
+
+template <int R, int I>
+__device__ __forceinline__ void power_products(float2* v, float2* pw) {
+  if constexpr (I < R) {
+    constexpr int hb = high_bit(I);
+    if constexpr (hb != I) pw[I] = c_mul(pw[hb], pw[I - hb]);
+    v[I] = c_mul(v[I], pw[I]);
+    power_products<R, I + 1>(v, pw);
+  }
+}
+
+template <int R>
+__device__ __forceinline__ void apply_powers(float2* v, const float2* tw, unsigned e, int sign) {
+  if constexpr (R > 16) {
+#pragma unroll
+    for (int i = 1; i < R; ++i) v[i] = c_mul(v[i], tw_lookup(tw, (long long)(e * (unsigned)i), sign));
+  } else {
+    float2 pw[R];
+#pragma unroll
+    for (int i = 1; i < R; i *= 2) pw[i] = tw_lookup(tw, (long long)(e * (unsigned)i), sign);
+    power_products<R, 1>(v, pw);
+  }
+}
+
+// One Stockham stage of radix R over the tile.  GIN / GOUT: the inputs come
+// from the input order, the outputs go to the output order.
+template <int R, bool GIN, bool GOUT>
+__device__ __forceinline__ void stage(PassArg arg, int si, const Tile& t,
+                                      const float2* __restrict__ in, float2* __restrict__ out,
+                                      const float2* A, float2* B) {
+  const PassDesc& p = fresh(arg);
+  const StageDesc& st = p.st[si];
+  const int n = st.n, stride = st.stride, Ns = st.Ns;
+  const int nr = n / R, per = p.L / R;
+  const bool across = GIN ? p.in.across : GOUT ? p.out.across : p.ls != 1;
+  const unsigned total = (unsigned)(across ? p.TP * per : t.n * per);
+  const bool whole = stride == 1 && n == p.L;   // one digit: no outer or inner index
+  for (unsigned bf = threadIdx.x; bf < total; bf += blockDim.x) {
+    int w;
+    unsigned q;
+    split_bf(p, st.f_per, per, across, bf, w, q);
+    if (w >= t.n) continue;
+    unsigned l_lo = 0, j = q, l_hi = 0;
+    if (!whole) {
+      const unsigned a = fast_div(q, st.f_stride);
+      l_lo = q - a * (unsigned)stride;
+      l_hi = fast_div(a, st.f_nr);
+      j = a - l_hi * (unsigned)nr;
+    }
+    const unsigned jd = fast_div(j, st.f_Ns);
+    const unsigned jm = j - jd * (unsigned)Ns;
+    const int base = (int)(l_hi * (unsigned)(n * stride) + l_lo);
+    const int in0 = base + (int)j * stride, in_step = nr * stride;
+    const int out0 = base + (int)(jd * (unsigned)(Ns * R) + jm) * stride, out_step = Ns * stride;
+    Pencil pc{0, 0, 0};
+    if (GIN || GOUT) pc = pencil_of(p, t, w);
+    float2 v[R];
+    if constexpr (GIN) {
+      unsigned off[R];
+      offsets<R, false>(p, p.in, pc, in0, in_step, off);
+      const float2* src = in + pc.b * p.in.bstride;
+#pragma unroll
+      for (int i = 0; i < R; ++i) v[i] = src[off[i]];
+    } else {
+      const int e0 = in0 * p.ls + w * p.ws, es = in_step * p.ls;
+#pragma unroll
+      for (int i = 0; i < R; ++i) v[i] = A[mphys(e0 + i * es)];
+    }
+    if (Ns > 1) apply_powers<R>(v, dev_ptr(st.tw), (unsigned)(n / (Ns * R)) * jm, p.sign);
+    if constexpr (GOUT) {
+      dft_small<R>(v, p.sign);
+      unsigned off[R];
+      offsets<R, false>(p, p.out, pc, out0, out_step, off);
+      float2* dst = out + pc.b * p.out.bstride;
+      if (p.post) {
+        // the stage's digit is the last one (stride 1) or l's position in it
+        // does not change over the butterfly
+        const unsigned lo = post_lo(p, pc.s);
+        const unsigned x0 = post_pos(p, (unsigned)out0) * lo;
+        const unsigned xs = stride == 1 ? (unsigned)Ns * lo : 0u;
+#pragma unroll
+        for (int i = 0; i < R; ++i) v[i] = c_mul(v[i], post_twiddle(p, x0 + (unsigned)i * xs));
+      }
+#pragma unroll
+      for (int i = 0; i < R; ++i) dst[off[i]] = make_float2(v[i].x * p.scale, v[i].y * p.scale);
+    } else {
+      const int e0 = out0 * p.ls + w * p.ws, es = out_step * p.ls;
+      if constexpr (R > 16) {
+        dft_odd_emit<R>(v, p.sign, [&](int k, float2 x) { B[mphys(e0 + k * es)] = x; });
+      } else {
+        dft_small<R>(v, p.sign);
+#pragma unroll
+        for (int i = 0; i < R; ++i) B[mphys(e0 + i * es)] = v[i];
+      }
+    }
+  }
+}
+
+// A stage of any radix: one thread per output, the inputs from LDS (lanes of
+// one butterfly read the same word), the root's exponent kept by addition.
+__device__ __forceinline__ void stage_sum(PassArg arg, int si, const Tile& t,
+                                       const float2* A, float2* B) {
+  const PassDesc& p = fresh(arg);
+  const StageDesc& st = p.st[si];
+  const int R = st.radix, n = st.n, stride = st.stride, Ns = st.Ns;
+  const int nr = n / R;
+  const unsigned total = (unsigned)t.n * (unsigned)p.L;
+  for (unsigned e = threadIdx.x; e < total; e += blockDim.x) {
+    const int w = (int)fast_div(e, p.f_L);
+    const int l = (int)(e - (unsigned)w * (unsigned)p.L);
+    // output position l: digits (l_hi, idx, l_lo) with
+    // idx = jd Ns R + k Ns + jm
+    const int a = l / stride, l_lo = l - a * stride;
+    const int l_hi = a / n, idx = a - l_hi * n;
+    const int jd = idx / (Ns * R), rem = idx - jd * (Ns * R);
+    const int k = rem / Ns, jm = rem - k * Ns;
+    const int j = jd * Ns + jm;
+    const int base = l_hi * n * stride + l_lo;
+    // input i carries exp(sign 2 pi i (tstep i + nr ((i k) mod R)) / n)
+    const int inc = (int)(((long long)(n / (Ns * R)) * jm + (long long)nr * k) % n);
+    int x = 0;
+    float2 acc = make_float2(0.f, 0.f);
+    int pos = (base + j * stride) * p.ls + w * p.ws;
+    const int step = nr * stride * p.ls;
+    for (int i = 0; i < R; ++i) {
+      acc = c_add(acc, c_mul(A[mphys(pos)], tw_lookup(dev_ptr(st.tw), x, p.sign)));
+      pos += step;
+      x += inc;
+      x -= x >= n ? n : 0;
+    }
+    B[mphys(l * p.ls + w * p.ws)] = acc;
+  }
+}
+
+#define LFFT_SMALL_RADIX(X) \
+  X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+#define LFFT_MIXED_PRIME(X) X(17) X(19) X(23) X(29) X(31)
+
+// WIDE: 2^30 points and more, 64-bit coordinates; the input and the output
+// then move through LDS one element at a time (registers).
+template <bool WIDE>
+__global__ void __launch_bounds__(kPassThreads)
+    fft_mixed_kernel(PassDesc, const float2* __restrict__ in, float2* __restrict__ out) {
+  extern __shared__ float2 lds[];
+  const PassArg arg = (PassArg)__builtin_amdgcn_kernarg_segment_ptr();
+  const PassDesc& p = *(const PassDesc*)arg;
+  const int half = mphys(p.ls == 1 ? p.TP * p.ws : p.L * p.ls) + 1;
+  float2* A = lds;
+  float2* B = lds + half;
+  const long long OS = (long long)p.O * p.S, npen = p.batch * OS;
+  const long long pen0 = xcd_tile(blockIdx.x, gridDim.x) * p.TP;
+  Tile t;
+  t.b0 = pen0 / OS;
+  t.r0 = (int)(pen0 - t.b0 * OS);
+  t.n = (int)(npen - pen0 < p.TP ? npen - pen0 : p.TP);
+
+  const int last = p.nst - 1;
+  const bool gin = !WIDE && p.nst > 0 && p.st[0].radix <= 16;
+  const bool gout = !WIDE && p.nst > 0 && p.st[last].radix <= 16;
+  if (!gin) {
+    const bool across = p.in.across;
+    const unsigned total = (unsigned)((across ? p.TP : t.n) * p.L);
+    for (unsigned e = threadIdx.x; e < total; e += blockDim.x) {
+      int w;
+      unsigned l;
+      split_bf(p, p.f_L, p.L, across, e, w, l);
+      if (w >= t.n) continue;
+      const Pencil pc = pencil_of(p, t, w);
+      unsigned off[1];
+      offsets<1, WIDE>(p, p.in, pc, (int)l, 0, off);
+      A[mphys((int)l * p.ls + w * p.ws)] = in[pc.b * p.in.bstride + off[0]];
+    }
+    __syncthreads();
+  }
+  for (int si = 0; si < p.nst; ++si) {
+    const int radix = p.st[si].radix;
+    const bool first = si == 0 && gin, end = si == last && gout;
+    bool done = false;
+    if constexpr (!WIDE) {
+      if (first && end) {
+        switch (radix) {
+#define X(R) case R: stage<R, true, true>(arg, si, t, in, out, A, B); break;
+          LFFT_SMALL_RADIX(X)
+#undef X
+        }
+        return;
+      }
+      if (first) {
+        done = true;
+        switch (radix) {
+#define X(R) case R: stage<R, true, false>(arg, si, t, in, out, A, B); break;
+          LFFT_SMALL_RADIX(X)
+#undef X
+        }
+      } else if (end) {
+        switch (radix) {
+#define X(R) case R: stage<R, false, true>(arg, si, t, in, out, A, B); break;
+          LFFT_SMALL_RADIX(X)
+#undef X
+        }
+        return;
+      }
+    }
+    if (!done) {
+      switch (radix) {
+#define X(R) case R: stage<R, false, false>(arg, si, t, in, out, A, B); break;
+        LFFT_SMALL_RADIX(X)
+        LFFT_MIXED_PRIME(X)
+#undef X
+        default: stage_sum(arg, si, t, A, B); break;
+      }
+    }
+    __syncthreads();
+    float2* x = A;
+    A = B;
+    B = x;
+  }
+  const bool across = p.out.across;
+  const unsigned total = (unsigned)((across ? p.TP : t.n) * p.L);
+  for (unsigned e = threadIdx.x; e < total; e += blockDim.x) {
+    int w;
+    unsigned l;
+    split_bf(p, p.f_L, p.L, across, e, w, l);
+    if (w >= t.n) continue;
+    const Pencil pc = pencil_of(p, t, w);
+    unsigned off[1];
+    offsets<1, WIDE>(p, p.out, pc, (int)l, 0, off);
+    float2 v = A[mphys((int)l * p.ls + w * p.ws)];
+    if (p.post) v = c_mul(v, post_twiddle(p, post_pos(p, l) * post_lo(p, pc.s)));
+    out[pc.b * p.out.bstride + off[0]] = make_float2(v.x * p.scale, v.y * p.scale);
+  }
+}
+
+template <bool WIDE>
+hipError_t launch_mixed_t(const PassDesc& p, const float2* in, float2* out, hipStream_t s) {
+  static std::atomic<bool> attr{false};
+  if (!attr.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)fft_mixed_kernel<WIDE>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+    attr.store(true, std::memory_order_release);
+  }
+  const long long npen = p.batch * (long long)p.O * p.S;
+  const long long tiles = (npen + p.TP - 1) / p.TP;
+  const int span = p.ls == 1 ? p.TP * p.ws : p.L * p.ls;
+  const size_t lds = (size_t)2 * (span + span / 16 + 1) * sizeof(float2);
+  if (tiles <= 0) return hipSuccess;
+  if (tiles > 0x7fffffffLL || lds > 160 * 1024 || p.NT < 64 || p.NT > kPassThreads)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(fft_mixed_kernel<WIDE>, dim3((unsigned)tiles), dim3(p.NT), lds, s, p, in, out);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+const char* pass_kernel_name(const PassDesc& p) {
+  if (p.kind == 3) return mfma_kernel_name(p);
+  if (p.kind == 2) return stream_kernel_name(p);
+  return p.kind == 1 ? fast_kernel_name(p)
+                     : p.wide ? "fft_mixed_kernel<true>" : "fft_mixed_kernel<false>";
+}
+
+hipError_t launch_pass(const PassDesc& p, const float2* in, float2* out, hipStream_t s) {
+  if (p.kind == 3) return launch_mfma_pass(p, in, out, s);
+  if (p.kind == 2) return launch_stream_pass(p, in, out, s);
+  if (p.kind == 1) return launch_fast_pass(p, in, out, s);
+  return p.wide ? launch_mixed_t<true>(p, in, out, s) : launch_mixed_t<false>(p, in, out, s);
+}
+
+}  // namespace lfft

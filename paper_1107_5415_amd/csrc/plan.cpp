@@ -26,7 +26,8 @@ namespace {
 constexpr i64 kMaxPencil = 8192;   // longest digit handled on chip
 constexpr i64 kMaxTile = 8192;     // elements of one single-pass tile
 constexpr i64 kMaxBlueAxis = i64(1) << 23;   // longest chirp-z axis (convolution <= 2^24)
-constexpr i64 kTileTarget = 4096;  // elements per tile for short pencils
+constexpr i64 kTileTarget = 4096;  // elements per tile for short pencils (mixed-radix kernel)
+constexpr i64 kTilesWanted = 768;  // three tiles per CU
 // pyramid levels whose channel (all signals) has at most this many points
 // run their channel FFTs in one batched launch
 constexpr i64 kChannelBatchElems = i64(1) << 22;
@@ -83,47 +84,81 @@ Side freq_side(const Smith& S, const Mat& A) {
   return s;
 }
 
+// Multiply-shift division by d (1 <= d < 2^31); checked on boundary values.
+FastDiv make_fast_div(i64 d) {
+  if (d < 1 || d >= (i64(1) << 31)) throw StatusError{E_STATE};
+  int sh = 0;
+  while ((i64(1) << sh) < d) ++sh;
+  const unsigned long long mag = ((1ull << (31 + sh)) / (unsigned long long)d) + 1;
+  if (mag >> 32) throw StatusError{E_STATE};
+  FastDiv f{(unsigned)mag, sh};
+  const i64 top = (i64(1) << 31) - 1;
+  const i64 probes[] = {0, 1, d - 1, d, d + 1, top, top - 1, (top / d) * d, (top / d) * d - 1};
+  for (i64 n : probes)
+    if (n >= 0 && n <= top && (i64)fast_div((unsigned)n, f) != n / d) throw StatusError{E_STATE};
+  return f;
+}
+
+// Radices of the mixed-radix kernel for a digit of length n: the fewest
+// stages of radix 2 .. 16 or a prime (an LDS round trip and a barrier each),
+// then the smallest sum.  Primes above 16 go between the others where they
+// can: the first and the last stage of a pass load and store through the maps
+// without a pass over LDS only up to radix 16.
 std::vector<int> radices_of(i64 n) {
-  std::vector<int> r;
-  while (n % 16 == 0 && n > 16 * 1) {
-    r.push_back(16);
-    n /= 16;
-  }
-  // remaining power of two as one radix from {2,4,8,16}
-  if (n % 16 == 0) {
-    r.push_back(16);
-    n /= 16;
-  } else if (n % 8 == 0) {
-    r.push_back(8);
-    n /= 8;
-  } else if (n % 4 == 0) {
-    r.push_back(4);
-    n /= 4;
-  } else if (n % 2 == 0) {
-    r.push_back(2);
-    n /= 2;
-  }
-  for (i64 p = 3; n > 1; p += 2) {
-    while (n % p == 0) {
-      r.push_back((int)p);
-      n /= p;
+  std::vector<i64> divs, cand;
+  for (i64 c = 1; c <= n; ++c)
+    if (n % c == 0) divs.push_back(c);
+  i64 rest = n;
+  for (i64 q = 2; q <= 16; ++q)
+    if (n % q == 0) cand.push_back(q);
+  for (i64 q = 2; q * q <= rest; ++q)
+    while (rest % q == 0) {
+      if (q > 16 && cand.back() != q) cand.push_back(q);
+      rest /= q;
     }
-    if (p * p > n && n > 1) {
-      r.push_back((int)n);
-      n = 1;
+  if (rest > 16 && (cand.empty() || cand.back() != rest)) cand.push_back(rest);
+  // per divisor: stages, sum of the radices, the radix taken
+  std::vector<std::array<i64, 3>> best(divs.size(), {{1000, 0, 0}});
+  best[0] = {{0, 0, 1}};
+  for (size_t k = 1; k < divs.size(); ++k)
+    for (i64 r : cand) {
+      if (divs[k] % r != 0) continue;
+      const size_t at = std::lower_bound(divs.begin(), divs.end(), divs[k] / r) - divs.begin();
+      const std::array<i64, 3> t{{best[at][0] + 1, best[at][1] + r, r}};
+      if (t < best[k]) best[k] = t;
     }
+  std::vector<int> small, large, out;
+  for (i64 c = n; c > 1;) {
+    const i64 r = best[std::lower_bound(divs.begin(), divs.end(), c) - divs.begin()][2];
+    (r > 16 ? large : small).push_back((int)r);
+    c /= r;
   }
-  return r;
+  std::sort(small.rbegin(), small.rend());
+  if (!small.empty()) out.push_back(small.front());
+  out.insert(out.end(), large.begin(), large.end());
+  if (small.size() > 1) out.insert(out.end(), small.begin() + 1, small.end());
+  return out;
 }
 
 bool is_pow2(i64 n) { return n > 0 && (n & (n - 1)) == 0; }
 
-// Two on-chip digits n = hi * lo (lo the longest divisor of at most
-// kMaxPencil points with hi = n / lo on chip too); 0 if there is none.
-i64 two_digit_lo(i64 n) {
-  for (i64 c = kMaxPencil; c >= 2; --c)
-    if (n % c == 0 && n / c <= kMaxPencil) return c;
-  return 0;
+// Two on-chip digits n = hi * lo of at most kMaxPencil points each, 0 if
+// there are none.  Powers of two: the longest lo.  Other cycles run on the
+// mixed-radix kernel, whose tiles hold several pencils only of short ones:
+// the split with the shortest longer pencil, where the high digit takes the
+// whole axes before it (`lead` points) along while they fit.
+i64 two_digit_lo(i64 n, i64 lead) {
+  i64 best = 0, best_len = 0;
+  for (i64 c = kMaxPencil; c >= 2; --c) {
+    if (n % c != 0 || n / c > kMaxPencil) continue;
+    if (is_pow2(n)) return c;
+    const i64 hi = n / c, len = std::max(c, hi * lead <= kMaxPencil ? hi * lead : hi);
+    if (!best || len < best_len) {
+      best = c;
+      best_len = len;
+    }
+  }
+  return best;
 }
 
 // Three on-chip digits n = n1 * n2 * n3 for cycles beyond two pencils.  The
@@ -321,6 +356,34 @@ std::vector<int4> linear_table(const std::vector<i64>& eps, const std::vector<Di
   return t;
 }
 
+// Whether a step to the next pencil is shorter in memory on this side than a
+// step along the pencil (digits [a, b)): then neighbouring threads of the
+// mixed-radix kernel take neighbouring pencils.
+bool across_of(const Side& side, const std::vector<Digit>& dg, int a, int b, bool out_weights) {
+  auto step = [&](int lo, int hi) -> i64 {
+    int g = hi - 1;
+    while (g >= lo && dg[g].n < 2) --g;
+    if (g < lo) return -1;
+    const i64 w = out_weights ? dg[g].w_out : dg[g].w_in;
+    const Vec4 v = scale4(side.H, side.unit[dg[g].axis], w);
+    Vec4 r = zero4();
+    for (int i = 0; i < 4; ++i) r[i] = -v[i];
+    r = reduce4(side.H, r);
+    i64 f = 0, k = 0;
+    for (int i = 0; i < side.H.d; ++i) {
+      f = f * side.H.a[i][i] + v[i];
+      k = k * side.H.a[i][i] + r[i];
+    }
+    return std::min(f, k);
+  };
+  const int D = (int)dg.size();
+  i64 pen = step(b, D);
+  if (pen < 0) pen = step(0, a);
+  const i64 along = step(a, b);
+  if (pen < 0 || along < 0) return pen >= 0;
+  return pen < along;
+}
+
 MapDesc natural_map(Blob& blob, const Side& side, int d, const std::vector<Digit>& dg, int a,
                     int b, bool out_weights) {
   MapDesc m{};
@@ -337,12 +400,14 @@ MapDesc natural_map(Blob& blob, const Side& side, int d, const std::vector<Digit
   m.To = blob.ref(natural_table(side, dg, 0, a, out_weights));
   m.Tl = blob.ref(natural_table(side, dg, a, b, out_weights));
   m.Ts = blob.ref(natural_table(side, dg, b, (int)dg.size(), out_weights));
+  m.across = across_of(side, dg, a, b, out_weights) ? 1 : 0;
   return m;
 }
 
-MapDesc identity_map() {
+MapDesc identity_map(bool across) {
   MapDesc m{};
   m.mode = MAP_IDENTITY;
+  m.across = across ? 1 : 0;
   return m;
 }
 
@@ -422,6 +487,35 @@ i64 batch_pencils(const LatticePlan* p, const PassDesc& pd) {
   return p->batch * (i64)pd.O * pd.S;
 }
 
+// Tile of a mixed-radix pass: up to 4096 elements (one pencil if it is
+// longer), fewer while that leaves less than three tiles per CU, but column
+// tiles keep 16 pencils (whole 128-byte segments) and short rows 256
+// elements; one thread per 8 elements.
+void mixed_shape(const LatticePlan* p, PassDesc& pd) {
+  const i64 npen = batch_pencils(p, pd);
+  const i64 cap = std::max<i64>(1, kTileTarget / pd.L);
+  const i64 least = pd.S > 1 ? 16 : (256 + pd.L - 1) / pd.L;
+  i64 tp = std::max(least, npen / kTilesWanted);
+  tp = std::min(std::min(tp, cap), npen);
+  pd.TP = (int)tp;
+  pd.NT = (int)std::min<i64>(1024, std::max<i64>(64, (tp * pd.L / 8 + 63) / 64 * 64));
+  if (pd.S > 1 && tp > 1) {
+    pd.ls = (int)(tp >= 8 ? tp | 1 : tp);   // odd: no bank conflicts along a pencil
+    pd.ws = 1;
+  } else {
+    pd.ls = 1;
+    pd.ws = pd.L | 1;
+  }
+  pd.wide = p->m >= (i64(1) << 30) ? 1 : 0;
+  pd.f_TP = make_fast_div(pd.TP);
+  pd.f_S = make_fast_div(pd.S);
+  pd.f_OS = make_fast_div((i64)pd.O * pd.S);
+  pd.f_L = make_fast_div(pd.L);
+  pd.f_lmod = make_fast_div(pd.post ? pd.post_lmod : 1);
+  pd.f_lodiv = make_fast_div(pd.post ? pd.lo_div : 1);
+  pd.f_lon = make_fast_div(pd.post ? pd.lo_n : 1);
+}
+
 void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& out_side, int sign,
                   TwCache& tw) {
   E.sign = sign;
@@ -437,12 +531,6 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
     pd.O = (int)range_count(dg, 0, R.a);
     pd.L = (int)range_count(dg, R.a, R.b);
     pd.S = (int)range_count(dg, R.b, D);
-    i64 tp = std::max<i64>(1, kTileTarget / pd.L);
-    if (pd.S > 1) {
-      tp = std::min<i64>(tp, pd.S);
-      while (pd.S % tp) --tp;
-    }
-    pd.TP = (int)tp;
     // register-resident kernel for power-of-two pencils of at least 32 points
     bool pow2 = pd.L >= 32 && pd.L <= kMaxPencil && (p->m < (i64(1) << 30));
     for (int g = R.a; g < R.b; ++g) pow2 = pow2 && is_pow2(dg[g].n);
@@ -506,6 +594,12 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
         s.lg_n = ilog2(dg[g].n);
         s.lg_stride = ilog2(stride);
         s.lg_Ns = ilog2(Ns);
+        if (pd.kind == 0) {
+          s.f_stride = make_fast_div(stride);
+          s.f_nr = make_fast_div(dg[g].n / r);
+          s.f_Ns = make_fast_div(Ns);
+          s.f_per = make_fast_div(pd.L / r);
+        }
         Ns *= r;
       }
     }
@@ -533,25 +627,27 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
       pd.tw_hi = pr.first;
       pd.tw_lo = pr.second;
     }
-    pd.in = identity_map();
-    pd.out = identity_map();
+    if (pd.kind == 0) mixed_shape(p, pd);
+    pd.in = identity_map(pd.S > 1);
+    pd.out = identity_map(pd.S > 1);
     E.passes.push_back(pd);
   }
   // map variants of the first and the last pass
   const PassRange& R0 = p->ranges.front();
   const PassRange& R1 = p->ranges.back();
-  E.in_grid = identity_map();
+  E.in_grid = identity_map(E.passes.front().S > 1);
   E.in_nat = natural_map(p->blob, in_side, p->d, dg, R0.a, R0.b, false);
   E.has_nat_in = true;
   if (any_split) {
     MapDesc m{};
     m.mode = MAP_LINEAR;
+    m.across = E.passes.back().S > 1 ? 1 : 0;
     m.To = p->blob.ref(linear_table(p->eps, dg, 0, R1.a));
     m.Tl = p->blob.ref(linear_table(p->eps, dg, R1.a, R1.b));
     m.Ts = p->blob.ref(linear_table(p->eps, dg, R1.b, D));
     E.out_grid = m;
   } else {
-    E.out_grid = identity_map();
+    E.out_grid = identity_map(E.passes.back().S > 1);
   }
   E.out_nat = natural_map(p->blob, out_side, p->d, dg, R1.a, R1.b, true);
   E.has_nat_out = true;
@@ -643,7 +739,9 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
           if (n > kMaxTile) throw StatusError{E_UNSUPPORTED};
           p->digits.push_back(Digit{j, n, 0, 1, 1});
         } else {
-          i64 lo = two_digit_lo(n);
+          i64 lead = 1;
+          for (const Digit& g : p->digits) lead *= g.part == 0 ? g.n : 1;
+          i64 lo = two_digit_lo(n, lead);
           if (!lo) {
             // beyond two pencils: three on-chip digits with two four-step
             // twiddles (input index n1-digit * n2 n3 + n2-digit * n3 +
@@ -1047,21 +1145,6 @@ void exec_lattice(const LatticePlan* p, bool inverse, bool in_grid, bool out_gri
 // Wavelet plans (Section 5.3)
 
 namespace {
-// Multiply-shift division by d (1 <= d < 2^31); checked on boundary values.
-FastDiv make_fast_div(i64 d) {
-  if (d < 1 || d >= (i64(1) << 31)) throw StatusError{E_STATE};
-  int sh = 0;
-  while ((i64(1) << sh) < d) ++sh;
-  const unsigned long long mag = ((1ull << (31 + sh)) / (unsigned long long)d) + 1;
-  if (mag >> 32) throw StatusError{E_STATE};
-  FastDiv f{(unsigned)mag, sh};
-  const i64 top = (i64(1) << 31) - 1;
-  const i64 probes[] = {0, 1, d - 1, d, d + 1, top, top - 1, (top / d) * d, (top / d) * d - 1};
-  for (i64 n : probes)
-    if (n >= 0 && n <= top && (i64)fast_div((unsigned)n, f) != n / d) throw StatusError{E_STATE};
-  return f;
-}
-
 // (g0, y0 numerators, v) for |det J| = 2: g0 a unit vector outside J^T Z^d,
 // y0 = num/2 the non-zero point of P(J) in [-1/2, 1/2)^d, v = J y0.
 void dilation_data(const Mat& J, Vec4& g0, Vec4& v) {
