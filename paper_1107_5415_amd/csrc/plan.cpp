@@ -111,12 +111,11 @@ std::vector<int> radices_of(i64 n) {
   i64 rest = n;
   for (i64 q = 2; q <= 16; ++q)
     if (n % q == 0) cand.push_back(q);
-  for (i64 q = 2; q * q <= rest; ++q)
-    while (rest % q == 0) {
-      if (q > 16 && cand.back() != q) cand.push_back(q);
-      rest /= q;
-    }
-  if (rest > 16 && (cand.empty() || cand.back() != rest)) cand.push_back(rest);
+  for (i64 q = 2; q * q <= rest; ++q) {
+    if (q > 16 && rest % q == 0) cand.push_back(q);
+    while (rest % q == 0) rest /= q;
+  }
+  if (rest > 16) cand.push_back(rest);
   // per divisor: stages, sum of the radices, the radix taken
   std::vector<std::array<i64, 3>> best(divs.size(), {{1000, 0, 0}});
   best[0] = {{0, 0, 1}};
@@ -145,14 +144,16 @@ bool is_pow2(i64 n) { return n > 0 && (n & (n - 1)) == 0; }
 // Two on-chip digits n = hi * lo of at most kMaxPencil points each, 0 if
 // there are none.  Powers of two: the longest lo.  Other cycles run on the
 // mixed-radix kernel, whose tiles hold several pencils only of short ones:
-// the split with the shortest longer pencil, where the high digit takes the
-// whole axes before it (`lead` points) along while they fit.
+// the split with the shortest longer pencil, among those whose high digit
+// takes the whole axes before it (`lead` points) along if there are any (no
+// pass over those axes alone).
 i64 two_digit_lo(i64 n, i64 lead) {
   i64 best = 0, best_len = 0;
   for (i64 c = kMaxPencil; c >= 2; --c) {
     if (n % c != 0 || n / c > kMaxPencil) continue;
     if (is_pow2(n)) return c;
-    const i64 hi = n / c, len = std::max(c, hi * lead <= kMaxPencil ? hi * lead : hi);
+    const i64 hi = n / c, joint = hi * lead;
+    const i64 len = joint <= kMaxPencil ? std::max(c, joint) : kMaxPencil + std::max(c, hi);
     if (!best || len < best_len) {
       best = c;
       best_len = len;
