@@ -33,7 +33,7 @@ enum MapMode : int { MAP_IDENTITY = 0, MAP_LINEAR = 1, MAP_NATURAL = 2 };
 struct MapDesc {
   int mode;
   int d;
-  int across;                 // mixed-radix kernel: neighbouring threads on neighbouring
+  int across;                 // mixed-radix and chirp-z kernels: neighbouring threads on neighbouring
                               // pencils (0: on neighbouring positions of one pencil)
   int H[4][4];
   long long box_stride[4];
@@ -61,7 +61,8 @@ struct StageDesc {
 
 struct PassDesc {
   int kind;                   // 0 mixed-radix, 1 register-resident power-of-two, 2 streaming,
-                              // 3 split-BF16 MFMA, 4 chirp-z (one whole axis)
+                              // 3 split-BF16 MFMA, 4 chirp-z (a long axis),
+                              // 5 chirp-z on chip (one digit of at most 8192 points)
   int P;                      // fast kernel: points per thread (16 or 32)
   int W;                      // fast kernel: pencils per workgroup
   int split;                  // fast kernel: exchange real and imaginary parts separately
@@ -99,14 +100,20 @@ struct PassDesc {
   int lo_n;
   const float2* tw_hi;
   const float2* tw_lo;
-  // chirp-z pass (kind 4): the axis of length L as a cyclic convolution of
-  // length bN (a power of two >= 2L - 1); chirp[j] = exp(-pi i j^2 / L),
-  // bhat = the DFT of the convolution kernel conj(chirp) (forward sign;
-  // both conjugated for sign +1); blue = index of the plan's inner FFT
-  int bN;
-  int blue;
+  // chirp-z passes: the axis or digit of length L as a cyclic convolution of
+  // length bN (a power of two >= 2L - 1); chirp[j] = exp(-pi i j^2 / L), bhat =
+  // the DFT of the convolution kernel conj(chirp) over bN (both conjugated
+  // for sign +1).  Kind 4 (three launches): bN = bH R, element n = a R + c,
+  // bhat in the order (k mod bH, k / bH); tables exp(-2 pi i k / n) of the
+  // columns (tw_col, n = bH) and the rows (tw_row, n = R), and two-level for
+  // bN (cv_hi, cv_lo).  Kind 5 (one launch): tw_row for n = bN.
+  int bN, bH;
   const float2* chirp;
   const float2* bhat;
+  const float2* tw_row;
+  const float2* tw_col;
+  const float2* cv_hi;
+  const float2* cv_lo;
   MapDesc in, out;
 };
 

@@ -1,8 +1,8 @@
 // Mixed-radix FFT pass for gfx950: any pencil length up to 8192.  One
 // workgroup owns a tile of TP pencils that moves between two LDS buffers, one
 // Stockham stage per move; radices 2 .. 16 and the primes 17 .. 31 run in
-// registers, larger primes (only inside pencils of several digits, see
-// chirp_tile.hip for the others) as a sum shared by all threads.
+// registers, larger primes (only inside pencils of several digits; the others are
+// chirp-z passes) as a sum shared by all threads.
 //
 // The first stage reads its butterflies straight from the input order and the
 // last one writes straight to the output order, through the planner's maps
@@ -26,6 +26,7 @@
 
 #include "dft_small.hpp"
 #include "kernels.hpp"
+#include "pass_addr.hpp"
 
 namespace lfft {
 namespace {
@@ -42,117 +43,7 @@ __device__ __forceinline__ const PassDesc& fresh(PassArg k) {
   return *(const PassDesc*)k;
 }
 
-// a table pointer read from the descriptor points to device memory
-template <class T>
-__device__ __forceinline__ const T* dev_ptr(const T* x) {
-  return (const T*)(const __attribute__((address_space(1))) T*)x;
-}
-
 __device__ __forceinline__ int mphys(int e) { return e + (e >> 4); }
-
-struct Tile {
-  long long b0;    // signal of the tile's first pencil
-  int r0;          // its index o S + s inside the signal
-  int n;           // pencils of this tile
-};
-
-struct Pencil {
-  long long b;
-  int o, s;
-};
-
-__device__ __forceinline__ Pencil pencil_of(const PassDesc& p, const Tile& t, int w) {
-  const unsigned r = (unsigned)(t.r0 + w);
-  const unsigned q = fast_div(r, p.f_OS);
-  const unsigned i = r - q * (unsigned)(p.O * p.S);
-  Pencil c;
-  c.b = t.b0 + q;
-  c.o = (int)fast_div(i, p.f_S);
-  c.s = (int)(i - (unsigned)c.o * (unsigned)p.S);
-  return c;
-}
-
-// Element offsets (below 2^31) inside the signal of positions l0 + i step,
-// i < R, of one pencil; the positions differ in one digit only.
-template <int R, bool WIDE>
-__device__ __forceinline__ void offsets(const PassDesc& p, const MapDesc& m, const Pencil& c, int l0,
-                                        int step, unsigned* off) {
-  if (m.mode == MAP_IDENTITY) {
-    const unsigned a = ((unsigned)c.o * (unsigned)p.L + (unsigned)l0) * (unsigned)p.S + (unsigned)c.s;
-#pragma unroll
-    for (int i = 0; i < R; ++i) off[i] = a + (unsigned)(i * step) * (unsigned)p.S;
-  } else if (m.mode == MAP_LINEAR) {
-    const int4* Tl = dev_ptr(m.Tl);
-    const unsigned a = (unsigned)(dev_ptr(m.To)[c.o].x + dev_ptr(m.Ts)[c.s].x) + (unsigned)Tl[l0].x;
-    const unsigned d = R > 1 ? (unsigned)Tl[step].x : 0u;
-#pragma unroll
-    for (int i = 0; i < R; ++i) off[i] = a + (unsigned)i * d;
-  } else {
-    const int4 To = dev_ptr(m.To)[c.o], Ts = dev_ptr(m.Ts)[c.s], Tl = dev_ptr(m.Tl)[l0];
-    const int4 D = R > 1 ? dev_ptr(m.Tl)[step] : make_int4(0, 0, 0, 0);
-    if constexpr (WIDE) {
-      // coordinates past 2^30: 64-bit sums
-      long long x[4] = {0, 0, 0, 0};
-      group_add(m, x, To);
-      group_add(m, x, Ts);
-      group_add(m, x, Tl);
-#pragma unroll
-      for (int i = 0; i < R; ++i) {
-        long long k = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) k += x[j] * m.box_stride[j];
-        off[i] = (unsigned)k;
-        if (i + 1 < R) group_add(m, x, D);
-      }
-    } else if (m.d == 2) {
-      int c0 = To.x, c1 = To.y;
-      gadd2(m, c0, c1, Ts);
-      gadd2(m, c0, c1, Tl);
-      const int h11 = m.H[1][1];
-#pragma unroll
-      for (int i = 0; i < R; ++i) {
-        off[i] = (unsigned)(c0 * h11 + c1);
-        if (i + 1 < R) gadd2(m, c0, c1, D);
-      }
-    } else if (m.d == 3) {
-      int x[4] = {To.x, To.y, To.z, 0};
-      gadd3(m, x, Ts);
-      gadd3(m, x, Tl);
-#pragma unroll
-      for (int i = 0; i < R; ++i) {
-        off[i] = (unsigned)nat_index3(m, x);
-        if (i + 1 < R) gadd3(m, x, D);
-      }
-    } else {
-      int x[4] = {To.x, To.y, To.z, To.w};
-      gadd32(m, x, Ts);
-      gadd32(m, x, Tl);
-#pragma unroll
-      for (int i = 0; i < R; ++i) {
-        off[i] = (unsigned)nat_index_i(m, x);
-        if (i + 1 < R) gadd32(m, x, D);
-      }
-    }
-  }
-}
-
-// four-step twiddle exp(sign 2 pi i k lo / postN): k < post_lmod and
-// lo < lo_n, so the product stays below postN = post_lmod lo_n
-__device__ __forceinline__ float2 post_twiddle(const PassDesc& p, unsigned x) {
-  float2 w = c_mul(dev_ptr(p.tw_hi)[x >> 12], dev_ptr(p.tw_lo)[x & 4095]);
-  if (p.sign > 0) w.y = -w.y;
-  return w;
-}
-
-__device__ __forceinline__ unsigned post_lo(const PassDesc& p, int s) {
-  const unsigned q = fast_div((unsigned)s, p.f_lodiv);
-  return q - fast_div(q, p.f_lon) * (unsigned)p.lo_n;
-}
-
-// position of l in the pencil's last digit
-__device__ __forceinline__ unsigned post_pos(const PassDesc& p, unsigned l) {
-  return l - fast_div(l, p.f_lmod) * (unsigned)p.post_lmod;
-}
 
 // Butterfly index -> tile pencil and pencil-local butterfly, with
 // neighbouring indices across the pencils or along one.
@@ -198,7 +89,7 @@ __device__ __forceinline__ void apply_powers(float2* v, const float2* tw, unsign
 // One Stockham stage of radix R over the tile.  GIN / GOUT: the inputs come
 // from the input order, the outputs go to the output order.
 template <int R, bool GIN, bool GOUT>
-__device__ __forceinline__ void stage(PassArg arg, int si, const Tile& t,
+__device__ __forceinline__ void stage(PassArg arg, int si, const TileOf& t,
                                       const float2* __restrict__ in, float2* __restrict__ out,
                                       const float2* A, float2* B) {
   const PassDesc& p = fresh(arg);
@@ -271,7 +162,7 @@ __device__ __forceinline__ void stage(PassArg arg, int si, const Tile& t,
 
 // A stage of any radix: one thread per output, the inputs from LDS (lanes of
 // one butterfly read the same word), the root's exponent kept by addition.
-__device__ __forceinline__ void stage_sum(PassArg arg, int si, const Tile& t,
+__device__ __forceinline__ void stage_sum(PassArg arg, int si, const TileOf& t,
                                        const float2* A, float2* B) {
   const PassDesc& p = fresh(arg);
   const StageDesc& st = p.st[si];
@@ -320,12 +211,7 @@ __global__ void __launch_bounds__(kPassThreads)
   const int half = mphys(p.ls == 1 ? p.TP * p.ws : p.L * p.ls) + 1;
   float2* A = lds;
   float2* B = lds + half;
-  const long long OS = (long long)p.O * p.S, npen = p.batch * OS;
-  const long long pen0 = xcd_tile(blockIdx.x, gridDim.x) * p.TP;
-  Tile t;
-  t.b0 = pen0 / OS;
-  t.r0 = (int)(pen0 - t.b0 * OS);
-  t.n = (int)(npen - pen0 < p.TP ? npen - pen0 : p.TP);
+  const TileOf t = tile_of_pencils(p, xcd_tile(blockIdx.x, gridDim.x) * p.TP, p.TP);
 
   const int last = p.nst - 1;
   const bool gin = !WIDE && p.nst > 0 && p.st[0].radix <= 16;
@@ -427,6 +313,7 @@ hipError_t launch_mixed_t(const PassDesc& p, const float2* in, float2* out, hipS
 }  // namespace
 
 const char* pass_kernel_name(const PassDesc& p) {
+  if (p.kind >= 4) return chirp_kernel_name(p);
   if (p.kind == 3) return mfma_kernel_name(p);
   if (p.kind == 2) return stream_kernel_name(p);
   return p.kind == 1 ? fast_kernel_name(p)
@@ -434,6 +321,7 @@ const char* pass_kernel_name(const PassDesc& p) {
 }
 
 hipError_t launch_pass(const PassDesc& p, const float2* in, float2* out, hipStream_t s) {
+  if (p.kind == 5) return launch_chirp_tile(p, in, out, s);
   if (p.kind == 3) return launch_mfma_pass(p, in, out, s);
   if (p.kind == 2) return launch_stream_pass(p, in, out, s);
   if (p.kind == 1) return launch_fast_pass(p, in, out, s);

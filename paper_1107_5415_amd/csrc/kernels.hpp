@@ -87,13 +87,16 @@ hipError_t launch_unsplit_q_mask_grad(const SplitQDesc& sd, long long batch, con
                                       const float* mask, const float2* g, long long g_bs,
                                       float* gmask, hipStream_t s);
 
-// Chirp-z pass (kind 4), three steps around the inner FFTs of length p.bN:
-// A[pen][j] = x(pen, j) chirp[j] for j < L, 0 up to bN (gather through p.in);
-// B[pen][k] *= bhat[k]; out(pen, k) = A[pen][k] chirp[k] scale (scatter
-// through p.out).  npen = batch * O * S pencils.
-hipError_t launch_blue_pre(const PassDesc& p, const float2* in, float2* A, hipStream_t s);
-hipError_t launch_blue_mul(const PassDesc& p, float2* B, hipStream_t s);
-hipError_t launch_blue_post(const PassDesc& p, const float2* A, float2* out, hipStream_t s);
+// Chirp-z on chip (kind 5): one launch.
+hipError_t launch_chirp_tile(const PassDesc& p, const float2* in, float2* out, hipStream_t s);
+// Chirp-z pass of a long axis (kind 4), three launches over A[pencil][bN]:
+// gather, chirp and column FFTs; rows (FFT, product with bhat, inverse FFT)
+// in place; inverse column FFTs, chirp and scatter.
+hipError_t launch_chirp_in(const PassDesc& p, const float2* in, float2* A, hipStream_t s);
+hipError_t launch_chirp_rows(const PassDesc& p, float2* A, hipStream_t s);
+hipError_t launch_chirp_out(const PassDesc& p, const float2* A, float2* out, hipStream_t s);
+// Kernel names for tracing; step 0 .. 2 of a long axis.
+const char* chirp_kernel_name(const PassDesc& p, int step = 0);
 
 // data[b * bstride + idx[i]] *= fac[r[i]] for every listed class i < n and
 // signal b < batch (the Dirichlet kernel's boundary classes, Section 6.2).

@@ -16,6 +16,7 @@
 #include <mutex>
 
 #include "batch.hpp"
+#include "chirp.hpp"
 #include "fiber.hpp"
 #include "kernels.hpp"
 #include "ktrace.hpp"
@@ -141,22 +142,44 @@ std::vector<int> radices_of(i64 n) {
 
 bool is_pow2(i64 n) { return n > 0 && (n & (n - 1)) == 0; }
 
+// smallest power of two of at least max(2n - 1, 128) points
+i64 chirp_length(i64 n) {
+  i64 N = 128;
+  while (N < 2 * n - 1) N *= 2;
+  return N;
+}
+
+// a prime factor too large for a register butterfly
+bool large_prime(i64 n) {
+  for (i64 q = 2; q <= 31; ++q)
+    while (n % q == 0) n /= q;
+  return n > 1;
+}
+
 // Two on-chip digits n = hi * lo of at most kMaxPencil points each, 0 if
-// there are none.  Powers of two: the longest lo.  Other cycles run on the
-// mixed-radix kernel, whose tiles hold several pencils only of short ones:
-// the split with the shortest longer pencil, among those whose high digit
-// takes the whole axes before it (`lead` points) along if there are any (no
-// pass over those axes alone).
+// there are none.  Powers of two: the longest lo.  Other cycles: the high
+// digit takes the whole axes before it (`lead` points) along if it can (no
+// pass over those axes alone), large primes go into as few and as short
+// convolutions as possible (a chirp-z pass moves and transforms
+// chirp_length(L) / L values per point, and no other axis joins it), and then
+// the longer pencil is as short as possible (the tiles of the mixed-radix
+// kernel hold several pencils only of short ones).
 i64 two_digit_lo(i64 n, i64 lead) {
-  i64 best = 0, best_len = 0;
+  i64 best = 0;
+  double best_cost = 0;
   for (i64 c = kMaxPencil; c >= 2; --c) {
     if (n % c != 0 || n / c > kMaxPencil) continue;
     if (is_pow2(n)) return c;
-    const i64 hi = n / c, joint = hi * lead;
-    const i64 len = joint <= kMaxPencil ? std::max(c, joint) : kMaxPencil + std::max(c, hi);
-    if (!best || len < best_len) {
+    const i64 hi = n / c;
+    const bool big = large_prime(hi);
+    const bool joint = lead == 1 || (!big && hi * lead <= kMaxPencil);
+    double cost = joint ? 0.0 : 2.0;
+    for (i64 L : {c, hi})
+      if (large_prime(L)) cost += 1.0 + 0.5 * (double)chirp_length(L) / (double)L;
+    cost += (double)std::max(c, !big && joint ? hi * lead : hi) / (double)kMaxPencil;
+    if (!best || cost < best_cost) {
       best = c;
-      best_len = len;
+      best_cost = cost;
     }
   }
   return best;
@@ -215,12 +238,12 @@ std::vector<int> pow2_radices(i64 n) {
   return r;
 }
 
-// Chirp-z tables of one axis of length n: chirp[j] = exp(-pi i (j^2 mod 2n) / n)
-// for j < n, and the plain DFT of the convolution kernel b (b_t = conj(chirp)
-// at t and at N - t for 0 <= t < n, zero elsewhere) over N points, both built
-// in FP64 and rounded once.
-struct BlueTables {
-  i64 N;
+// Chirp-z tables of an axis or digit of length n: chirp[j] =
+// exp(-pi i (j^2 mod 2n) / n) for j < n, and the DFT of the convolution kernel
+// b (b_t = conj(chirp) at t and at N - t for 0 <= t < n, zero elsewhere) over
+// N points divided by N, in the order (k mod H, k / H); both built in FP64 and
+// rounded once.
+struct ChirpTables {
   const float2* chirp;
   const float2* bhat;
 };
@@ -234,12 +257,18 @@ void fft_host(std::vector<std::complex<double>>& a) {
     j ^= bit;
     if (i < j) std::swap(a[i], a[j]);
   }
+  std::vector<std::complex<double>> w(N / 2);
+  for (size_t k = 0; k < N / 2; ++k) {
+    const double ang = -2.0 * M_PI * (double)k / (double)N;
+    w[k] = std::complex<double>(std::cos(ang), std::sin(ang));
+  }
   for (size_t len = 2; len <= N; len <<= 1) {
+    const size_t step = N / len;
     for (size_t i = 0; i < N; i += len)
       for (size_t k = 0; k < len / 2; ++k) {
-        const double ang = -2.0 * M_PI * (double)k / (double)len;
-        const std::complex<double> w(std::cos(ang), std::sin(ang));
-        const std::complex<double> u = a[i + k], v = a[i + k + len / 2] * w;
+        const std::complex<double> u = a[i + k], x = a[i + k + len / 2], t = w[k * step];
+        const std::complex<double> v(x.real() * t.real() - x.imag() * t.imag(),
+                                     x.real() * t.imag() + x.imag() * t.real());
         a[i + k] = u + v;
         a[i + k + len / 2] = u - v;
       }
@@ -248,12 +277,10 @@ void fft_host(std::vector<std::complex<double>>& a) {
 
 struct TwCache {
   Blob* blob;
-  std::map<i64, BlueTables> blue;
-  BlueTables bluestein(i64 n) {
-    auto it = blue.find(n);
-    if (it != blue.end()) return it->second;
-    i64 N = 1;
-    while (N < 2 * n - 1) N *= 2;
+  std::map<i64, ChirpTables> chirps;
+  ChirpTables chirp(i64 n, i64 N, i64 H) {
+    auto it = chirps.find(n);
+    if (it != chirps.end()) return it->second;
     std::vector<std::complex<double>> c(n), b(N, 0.0);
     for (i64 j = 0; j < n; ++j) {
       const i64 r = (i64)(((i128)j * j) % (2 * n));
@@ -267,9 +294,12 @@ struct TwCache {
     fft_host(b);
     std::vector<float2> cf(n), bf(N);
     for (i64 j = 0; j < n; ++j) cf[j] = make_float2((float)c[j].real(), (float)c[j].imag());
-    for (i64 k = 0; k < N; ++k) bf[k] = make_float2((float)b[k].real(), (float)b[k].imag());
-    BlueTables t{N, blob->ref(cf), blob->ref(bf)};
-    blue[n] = t;
+    const i64 R = N / H;
+    for (i64 k = 0; k < N; ++k)
+      bf[(k % H) * R + k / H] =
+          make_float2((float)(b[k].real() / (double)N), (float)(b[k].imag() / (double)N));
+    ChirpTables t{blob->ref(cf), blob->ref(bf)};
+    chirps[n] = t;
     return t;
   }
   std::map<i64, const float2*> full;
@@ -507,8 +537,12 @@ void mixed_shape(const LatticePlan* p, PassDesc& pd) {
     pd.ls = 1;
     pd.ws = pd.L | 1;
   }
-  pd.wide = p->m >= (i64(1) << 30) ? 1 : 0;
   pd.f_TP = make_fast_div(pd.TP);
+}
+
+// index divisions of the kernels whose tiles cross signals
+void pass_divisions(const LatticePlan* p, PassDesc& pd) {
+  pd.wide = p->m >= (i64(1) << 30) ? 1 : 0;
   pd.f_S = make_fast_div(pd.S);
   pd.f_OS = make_fast_div((i64)pd.O * pd.S);
   pd.f_L = make_fast_div(pd.L);
@@ -567,18 +601,28 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
         pd.kind = 2;
     }
     pd.nst = 0;
-    if (R.b - R.a == 1 && dg[R.a].part == 3) {
-      // one whole axis by chirp-z: tables shared by every engine of the plan
-      pd.kind = 4;
-      int bi = 0;
-      for (int g = 0; g < R.a; ++g) bi += dg[g].part == 3 ? 1 : 0;
-      pd.blue = bi;
-      const BlueTables bt = tw.bluestein(dg[R.a].n);
-      pd.bN = (int)bt.N;
-      pd.chirp = bt.chirp;
-      pd.bhat = bt.bhat;
+    const bool one = R.b - R.a == 1;
+    if (one && dg[R.a].part == 3)
+      pd.kind = 4;   // a whole axis by chirp-z
+    else if (one && p->tile_lg == 0 && large_prime(pd.L) && p->m < (i64(1) << 30))
+      pd.kind = 5;
+    if (pd.kind >= 4) {
+      // tables shared by every engine of the plan
+      pd.bN = (int)chirp_length(pd.L);
+      pd.bH = pd.kind == 4 ? chirp_rows_of(pd.bN) : 1;
+      const ChirpTables ct = tw.chirp(pd.L, pd.bN, pd.bH);
+      pd.chirp = ct.chirp;
+      pd.bhat = ct.bhat;
+      pd.tw_row = tw.table(pd.bN / pd.bH);
+      if (pd.kind == 4) {
+        pd.tw_col = tw.table(pd.bH);
+        auto pr = tw.twolevel(pd.bN);
+        pd.cv_hi = pr.first;
+        pd.cv_lo = pr.second;
+      }
+      pd.W = pd.kind == 5 ? chirp_width(pd.bN) : 1;
     }
-    for (int g = R.a; g < R.b && pd.kind != 4; ++g) {
+    for (int g = R.a; g < R.b && pd.kind < 4; ++g) {
       int stride = (int)range_count(dg, g + 1, R.b);
       i64 Ns = 1;
       std::vector<int> rads = pd.kind == 1 ? pow2_radices(dg[g].n) : radices_of(dg[g].n);
@@ -629,6 +673,7 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
       pd.tw_lo = pr.second;
     }
     if (pd.kind == 0) mixed_shape(p, pd);
+    if (pd.kind == 0 || pd.kind >= 4) pass_divisions(p, pd);
     pd.in = identity_map(pd.S > 1);
     pd.out = identity_map(pd.S > 1);
     E.passes.push_back(pd);
@@ -672,6 +717,10 @@ void patch_engine(Engine& E, uintptr_t base) {
     patch(pd.tw_lo, base);
     patch(pd.chirp, base);
     patch(pd.bhat, base);
+    patch(pd.tw_row, base);
+    patch(pd.tw_col, base);
+    patch(pd.cv_hi, base);
+    patch(pd.cv_lo, base);
     patch_map(pd.in, base);
     patch_map(pd.out, base);
   }
@@ -802,6 +851,14 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
     } else if (p->m <= kMaxTile) {
       p->ranges.push_back(PassRange{0, Dg, false, 0});
     } else {
+      // a digit with a large prime is a chirp-z pass of its own (below 2^30
+      // points); others share passes up to one pencil
+      auto alone = [&](int g) {
+        return p->m < (i64(1) << 30) && large_prime(p->digits[g].n);
+      };
+      auto joins = [&](int g, i64 prod) {   // digit g joins the pass of digit g + 1 ..
+        return g >= 0 && p->digits[g].part == 0 && !alone(g) && prod * p->digits[g].n <= kMaxPencil;
+      };
       int i = Dg - 1;
       while (i >= 0) {
         if (p->digits[i].part == 2 && i >= 2 && p->digits[i - 1].part == 4) {
@@ -810,7 +867,7 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
           // each of the first two followed by its four-step twiddle
           int a = i - 2;
           i64 prod = p->digits[a].n;
-          while (a - 1 >= 0 && p->digits[a - 1].part == 0 && prod * p->digits[a - 1].n <= kMaxPencil) {
+          while (!alone(a) && joins(a - 1, prod)) {
             --a;
             prod *= p->digits[a].n;
           }
@@ -824,7 +881,7 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
           // alone); its four-step twiddle follows the pass
           int a = i - 1;
           i64 prod = p->digits[a].n;
-          while (a - 1 >= 0 && p->digits[a - 1].part == 0 && prod * p->digits[a - 1].n <= kMaxPencil) {
+          while (!alone(a) && joins(a - 1, prod)) {
             --a;
             prod *= p->digits[a].n;
           }
@@ -834,7 +891,7 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
         } else {
           int a = i;
           i64 prod = p->digits[i].n;
-          while (a - 1 >= 0 && p->digits[a - 1].part == 0 && prod * p->digits[a - 1].n <= kMaxPencil) {
+          while (!alone(a) && joins(a - 1, prod)) {
             --a;
             prod *= p->digits[a].n;
           }
@@ -844,17 +901,11 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
       }
     }
     p->ws_elems = p->ranges.size() > 1 ? (size_t)(p->m * batch) : 0;
-    // chirp-z axes: inner FFT plans and their share of the workspace
-    for (const auto& g : p->digits) {
-      if (g.part != 3) continue;
-      i64 N = 1;
-      while (N < 2 * g.n - 1) N *= 2;
-      const i64 pencils = batch * (p->m / g.n);
-      LatticePlan* in = build_lattice_plan(1, &N, pencils, flags & kPlanHostOnly);
-      p->blue.push_back(in);
-      p->blue_ws = std::max(p->blue_ws, (size_t)(2 * pencils * N) + in->ws_elems);
-    }
-    p->ws_elems += p->blue_ws;
+    // long chirp-z axes: the convolution's points of every pencil
+    for (const auto& g : p->digits)
+      if (g.part == 3)
+        p->chirp_ws = std::max(p->chirp_ws, (size_t)(batch * (p->m / g.n) * chirp_length(g.n)));
+    p->ws_elems += p->chirp_ws;
     TwCache tw{&p->blob, {}, {}, {}};
     Side fs = sample_side(p->Sf, p->M);
     Side ff = freq_side(p->Sf, p->M);
@@ -925,7 +976,6 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
 }
 
 void upload_plan(LatticePlan* p) {
-  for (LatticePlan* in : p->blue) upload_plan(in);
   if (p->dtab) return;
   p->dtab = upload_blob(p->blob);
   uintptr_t base = reinterpret_cast<uintptr_t>(p->dtab);
@@ -940,7 +990,6 @@ void free_plan(LatticePlan* p) {
   if (!p) return;
   if (p->dtab) (void)hipFree(p->dtab);
   if (p->dbnd) (void)hipFree(p->dbnd);
-  for (LatticePlan* in : p->blue) free_plan(in);
   delete p;
 }
 
@@ -1077,32 +1126,18 @@ void points(const LatticePlan* p, int which, i64* keys, i64* sym) {
 }
 
 namespace {
-// One chirp-z pass: gather with the chirp into A (pencils x N), A -> B by the
-// inner forward FFT, B times the kernel's DFT, B -> A by the inner inverse
-// FFT, scatter with the chirp and the pass's scale.  The inner FFTs are
-// unitary, so bhat carries the plain DFT of the kernel: F^{-1}(F a . bhat)
-// is the cyclic convolution.  wb: 2 pencils N + the inner plan's workspace.
+// A long chirp-z axis: three launches over A (pencils x N).
 void exec_chirp_z(const LatticePlan* p, const PassDesc& pd, const float2* src, float2* dst,
-                  float2* wb, hipStream_t s) {
-  const LatticePlan* in = p->blue[pd.blue];
-  const long long tot = in->batch * (long long)pd.bN;
-  float2* A = wb;
-  float2* B = wb + tot;
-  float2* iw = wb + 2 * tot;
-  const double by = 8.0 * (double)tot;
-  {
-    TraceScope ts(trace_on() ? "blue_pre_kernel" : nullptr, by + 8.0 * p->batch * p->m, s);
-    if (launch_blue_pre(pd, src, A, s) != hipSuccess) throw StatusError{E_HIP};
-  }
-  exec_lattice(in, false, false, false, A, B, iw, pd.bN, pd.bN, s);
-  {
-    TraceScope ts(trace_on() ? "blue_mul_kernel" : nullptr, 2.0 * by, s);
-    if (launch_blue_mul(pd, B, s) != hipSuccess) throw StatusError{E_HIP};
-  }
-  exec_lattice(in, true, false, false, B, A, iw, pd.bN, pd.bN, s);
-  {
-    TraceScope ts(trace_on() ? "blue_post_kernel" : nullptr, by + 8.0 * p->batch * p->m, s);
-    if (launch_blue_post(pd, A, dst, s) != hipSuccess) throw StatusError{E_HIP};
+                  float2* A, hipStream_t s) {
+  const double sig = 8.0 * (double)p->batch * (double)p->m;
+  const double by = 8.0 * (double)p->batch * (double)pd.O * (double)pd.S * (double)pd.bN;
+  for (int step = 0; step < 3; ++step) {
+    TraceScope ts(trace_on() ? chirp_kernel_name(pd, step) : nullptr, step == 1 ? 2 * by : by + sig,
+                  s);
+    const hipError_t e = step == 0   ? launch_chirp_in(pd, src, A, s)
+                         : step == 1 ? launch_chirp_rows(pd, A, s)
+                                     : launch_chirp_out(pd, A, dst, s);
+    if (e != hipSuccess) throw StatusError{E_HIP};
   }
 }
 }  // namespace

@@ -114,10 +114,7 @@ struct LatticePlan {
   // (r(h) > 0, Section 6.2), natural indices and r(h): the only frequencies
   // where the Dirichlet kernel's bracket sum differs from m^{-1/2}.  Built on
   // first use (build_boundary); dbnd holds [idx int64 x n][r int32 x n].
-  // chirp-z axes: the inner power-of-two FFT plan of each (batch = the
-  // axis's pencils), indexed by PassDesc::blue
-  std::vector<LatticePlan*> blue;
-  size_t blue_ws = 0;       // workspace of the chirp-z steps (after the pass buffer)
+  size_t chirp_ws = 0;      // workspace of long chirp-z axes (after the pass buffer)
   bool bnd_built = false;
   std::vector<i64> bnd_idx;
   std::vector<int> bnd_r;

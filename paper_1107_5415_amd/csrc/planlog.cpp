@@ -37,7 +37,7 @@ void log_engine(const LatticePlan* p, const Engine& E, const char* what) {
     // the streaming kernel runs its own compile-time radix sequence; the
     // other kernels run the descriptor's stages
     char stages[32] = "";
-    if (pd.kind != 2) std::snprintf(stages, sizeof stages, ", %d stages", pd.nst);
+    if (pd.kind < 2 || pd.kind == 3) std::snprintf(stages, sizeof stages, ", %d stages", pd.nst);
     std::fprintf(stderr, "lfft:   %-8s pass %d/%d %s pencil %d x %d per tile%s, O=%d S=%d%s%s%s%s%s\n",
                  what, i + 1, np, pass_kernel_name(pd), pd.L, pd.kind == 0 ? pd.TP : pd.W, stages, pd.O, pd.S,
                  pd.post ? ", four-step twiddle" : "", pd.in.mode == MAP_NATURAL ? ", natural in" : "",
