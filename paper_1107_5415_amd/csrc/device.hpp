@@ -7,7 +7,10 @@
 
 namespace lfft {
 
-constexpr int kMaxStages = 24;
+// Stages of one pass: within a digit of length n any two radices multiply to
+// more than 16, so a pencil of at most 8192 points in up to seven digits
+// needs no more.
+constexpr int kMaxStages = 12;
 
 // floor(n / d) for 0 <= n < 2^31 as (n * mag) >> (31 + sh), with
 // sh = ceil(log2 d) and mag = floor(2^(31 + sh) / d) + 1 < 2^32 (division by
@@ -33,14 +36,20 @@ enum MapMode : int { MAP_IDENTITY = 0, MAP_LINEAR = 1, MAP_NATURAL = 2 };
 struct MapDesc {
   int mode;
   int d;
-  int across;                 // mixed-radix and chirp-z kernels: neighbouring threads on neighbouring
-                              // pencils (0: on neighbouring positions of one pencil)
+  int across;                 // neighbouring threads on neighbouring pencils (0: on
+                              // neighbouring positions of one pencil); not in the
+                              // streaming and split-BF16 kernels
   int H[4][4];
   long long box_stride[4];
   long long bstride;          // batch stride in elements (LINEAR / NATURAL)
   const int4* To;
   const int4* Tl;
   const int4* Ts;
+  // register-resident kernel, last pass over rows: chain[t W + w] = (row,
+  // position) of tile t's w-th row and of the w-th of W consecutive natural
+  // elements, the first of which lies at position 0 of the tile's first row
+  // (NULL: rows in order)
+  const int2* chain;
 };
 
 // One Stockham stage: radix r on the pass digit of length n whose stride
@@ -74,7 +83,7 @@ struct PassDesc {
   int TP, NT;
   int ls, ws;
   int wide;
-  FastDiv f_TP, f_S, f_OS, f_L, f_lmod, f_lodiv, f_lon;
+  FastDiv f_TP, f_S, f_OS, f_L, f_lmod;
   int nst;
   StageDesc st[kMaxStages];
   int sign;                   // -1 forward, +1 inverse
@@ -89,8 +98,8 @@ struct PassDesc {
   // natural-order input (read once by the call): loads marked non-temporal,
   // so that the intermediate grid stays in the caches for the next pass
   int stream_in;
-  // four-step twiddle after the stages: x = ((l mod post_lmod) * lo) mod
-  // postN with lo = (s / lo_div) % lo_n, factor exp(sign 2 pi i x / postN)
+  // four-step twiddle after the stages: x = (l mod post_lmod) * lo with
+  // lo = (s / lo_div) % lo_n, below postN = post_lmod lo_n, factor exp(sign 2 pi i x / postN)
   // from the two-level table tw_hi[x >> 12] * tw_lo[x & 4095]; the high digit
   // is the last (fastest) digit of the pencil, of length post_lmod
   int post;
@@ -98,6 +107,7 @@ struct PassDesc {
   int post_lmod;
   int lo_div;
   int lo_n;
+  FastDiv f_lodiv, f_lon;
   const float2* tw_hi;
   const float2* tw_lo;
   // chirp-z passes: the axis or digit of length L as a cyclic convolution of

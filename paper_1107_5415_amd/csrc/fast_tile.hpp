@@ -46,6 +46,20 @@ __device__ __forceinline__ BfGeom geom(const StageDesc& st, int bl) {
   return g;
 }
 
+// Last stage of a one-digit pencil, butterfly `bl` turned by `off`
+// positions: with p = (bl + off) mod L the inputs of butterfly p mod Ns and
+// the twiddles of exponent p (instead of p mod Ns) give the outputs
+// p, p + Ns, ... mod L, the first one at p itself.
+__device__ __forceinline__ BfGeom geom_turned(const StageDesc& st, int bl, int off) {
+  BfGeom g;
+  g.jm = (bl + off) & (st.n - 1);
+  g.in0 = g.jm & (st.Ns - 1);
+  g.in_step = st.Ns;          // n / radix = Ns in the last stage
+  g.out0 = g.jm;
+  g.out_step = st.Ns;
+  return g;
+}
+
 // One side of a pencil: the signal's base pointer and 32-bit element
 // offsets inside the signal (the planner keeps these lattices below 2^30
 // points).
@@ -147,15 +161,17 @@ __device__ __forceinline__ void load_first(float2* v, const PassDesc& p, const A
 // 2^k < R with w = exp(-2 pi i jm / (Ns R)), read from the FP64-built table
 // of the digit.  Issued one stage ahead so their latency hides behind the
 // LDS exchange.
+// off >= 0: the turned last stage.
 template <int P, int R>
-__device__ __forceinline__ void prefetch_tw(float2* twb, const StageDesc& st, int jt, int TPP) {
+__device__ __forceinline__ void prefetch_tw(float2* twb, const StageDesc& st, int jt, int TPP,
+                                            int off) {
   constexpr int LG = R == 16 ? 4 : R == 8 ? 3 : R == 4 ? 2 : 1;
 #pragma unroll
   for (int q = 0; q < P / R; ++q) {
-    BfGeom g = geom(st, jt + TPP * q);
-    const int tstep = g.jm << (st.lg_n - st.lg_Ns - st.lg_r);
+    const int jm = off < 0 ? geom(st, jt + TPP * q).jm : geom_turned(st, jt + TPP * q, off).jm;
+    const int tstep = jm << (st.lg_n - st.lg_Ns - st.lg_r);
 #pragma unroll
-    for (int k = 0; k < LG; ++k) twb[q * LG + k] = st.tw[tstep << k];
+    for (int k = 0; k < LG; ++k) twb[q * LG + k] = st.tw[(tstep << k) & (st.n - 1)];
   }
 }
 
@@ -202,21 +218,22 @@ __device__ __forceinline__ void compute_stage(float2* v, const float2* twb, int 
   }
 }
 
-// LDS element index of pencil-local position l of tile pencil w
+// LDS element of pencil-local position l of tile pencil w: padded by one
+// element in 16; PR is the padded length of a row.
 template <bool COLS>
-__device__ __forceinline__ int lds_e(int l, int w, int W, int L) {
-  return COLS ? l * W + w : w * L + l;
+__device__ __forceinline__ int lds_e(int l, int w, int W, int PR) {
+  return COLS ? phys(l * W + w) : w * PR + phys(l);
 }
 
 template <int P, int R, bool COLS, int PART>
 __device__ __forceinline__ void lds_write(const float2* v, void* lds, const StageDesc& st, int jt,
-                                          int TPP, int w, int W, int L) {
+                                          int TPP, int w, int W, int PR) {
 #pragma unroll
   for (int q = 0; q < P / R; ++q) {
     BfGeom g = geom(st, jt + TPP * q);
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      int e = phys(lds_e<COLS>(g.out0 + i * g.out_step, w, W, L));
+      int e = lds_e<COLS>(g.out0 + i * g.out_step, w, W, PR);
       if constexpr (PART == 0)
         static_cast<float2*>(lds)[e] = v[q * R + i];
       else if constexpr (PART == 1)
@@ -229,13 +246,13 @@ __device__ __forceinline__ void lds_write(const float2* v, void* lds, const Stag
 
 template <int P, int R, bool COLS, int PART>
 __device__ __forceinline__ void lds_read(float2* v, const void* lds, const StageDesc& st, int jt,
-                                         int TPP, int w, int W, int L) {
+                                         int TPP, int w, int W, int PR, int off) {
 #pragma unroll
   for (int q = 0; q < P / R; ++q) {
-    BfGeom g = geom(st, jt + TPP * q);
+    const BfGeom g = off < 0 ? geom(st, jt + TPP * q) : geom_turned(st, jt + TPP * q, off);
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      int e = phys(lds_e<COLS>(g.in0 + i * g.in_step, w, W, L));
+      int e = lds_e<COLS>(g.in0 + i * g.in_step, w, W, PR);
       if constexpr (PART == 0)
         v[q * R + i] = static_cast<const float2*>(lds)[e];
       else if constexpr (PART == 1)
@@ -257,24 +274,20 @@ __device__ __forceinline__ void lds_read(float2* v, const void* lds, const Stage
 template <int P, int R, int MOUT>
 __device__ __forceinline__ void store_last_r(const float2* v, const PassDesc& p,
                                              const Addr<MOUT>& A, int jt, int TPP,
-                                             const Pencil& pc) {
+                                             const Pencil& pc, int off0) {
   const StageDesc& st = p.st[p.nst - 1];
   float2* out = const_cast<float2*>(A.base);
   const bool scaled = p.scale != 1.0f;
-  // four-step twiddle exponent ((l mod post_lmod) * lo) mod postN, lo fixed
-  // per pencil
-  const long long lo = p.post ? (pc.s / p.lo_div) % p.lo_n : 0;
+  // four-step twiddle exponent (l mod post_lmod) * lo, lo fixed per pencil
+  const unsigned lo = p.post ? post_lo(p, pc.s) : 0u;
 #pragma unroll
   for (int q = 0; q < P / R; ++q) {
-    BfGeom g = geom(st, jt + TPP * q);
+    const BfGeom g = off0 < 0 ? geom(st, jt + TPP * q) : geom_turned(st, jt + TPP * q, off0);
     for_positions<MOUT, R>(A, p.out, p.S, g.out0, g.out_step, [&](int i, int off) {
       float2 x = v[q * R + i];
       if (p.post) {
-        const int l = (g.out0 + i * g.out_step) % p.post_lmod;
-        const long long t = ((long long)l * lo) % p.postN;
-        float2 w = c_mul(p.tw_hi[t >> 12], p.tw_lo[t & 4095]);
-        if (p.sign > 0) w.y = -w.y;
-        x = c_mul(x, w);
+        const unsigned l = (unsigned)(g.out0 + i * g.out_step) & (unsigned)(p.post_lmod - 1);
+        x = c_mul(x, post_twiddle(p, l * lo));
       }
       if (scaled) {
         x.x *= p.scale;
@@ -287,17 +300,49 @@ __device__ __forceinline__ void store_last_r(const float2* v, const PassDesc& p,
 
 template <int P, int MOUT>
 __device__ __forceinline__ void store_last(const float2* v, const PassDesc& p, const Addr<MOUT>& A,
-                                           int jt, int TPP, const Pencil& pc) {
-  LFFT_RADIX_SWITCH(p.st[p.nst - 1].radix, (store_last_r<P, RR, MOUT>(v, p, A, jt, TPP, pc)));
+                                           int jt, int TPP, const Pencil& pc, int off) {
+  LFFT_RADIX_SWITCH(p.st[p.nst - 1].radix, (store_last_r<P, RR, MOUT>(v, p, A, jt, TPP, pc, off)));
+}
+
+// Pencil `pen` of the pass (inactive beyond the last one), rows in the order
+// of `chain` if there is one; off: its position offset there.
+__device__ __forceinline__ Pencil pencil_at(const PassDesc& p, long long pen, const int2* chain,
+                                            int& off) {
+  Pencil pc;
+  pc.active = pen < p.batch * (long long)p.O * p.S;
+  const long long pp = pc.active ? pen : 0;
+  const long long bo = pp / p.S;
+  pc.s = (int)(pp - bo * p.S);
+  pc.b = bo / p.O;
+  pc.o = (int)(bo - pc.b * p.O);
+  if (chain) {
+    const int2 c = chain[pc.o];
+    pc.o = c.x;
+    off = c.y;
+  }
+  return pc;
 }
 
 // Process tile `tile` of pass p with NT = W * L / P threads (tid < NT);
-// lds holds (W*L + W*L/16 + 1) float2 (SPLIT: floats).
+// lds holds (W*L + W*L/16 + kTilePad) float2 (SPLIT: floats).
+//
+// Row tiles of a last pass: natural neighbours lie in different rows unless
+// the axis is aligned with the natural order, and a thread order along the
+// row writes single elements to lines of their own.  The planner therefore
+// gathers the rows of W natural neighbours in one tile (chain: reading whole
+// rows costs the same in any order), and the last stage runs with
+// neighbouring threads on neighbouring rows, each row turned by the position
+// of its neighbour, so that a wave writes runs of W elements.  The change of
+// thread order rides on the last LDS exchange and the turn on the twiddles,
+// so neither costs anything.  The rows' LDS pitch is 32 / W elements modulo
+// 32 then, which spreads those reads over all banks.
+constexpr int kTilePad = 33;
+
 template <int P, bool COLS, bool SPLIT, int MIN, int MOUT>
 __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int tid,
                                           const float2* __restrict__ in,
                                           float2* __restrict__ out, void* lds) {
-  const int L = p.L, S = p.S, O = p.O, W = p.W;
+  const int L = p.L, S = p.S, W = p.W;
   const int TPP = L / P;
   int w, jt;
   if (COLS) {
@@ -307,17 +352,11 @@ __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int
     w = tid / TPP;
     jt = tid - w * TPP;
   }
-  Pencil pc;
-  const long long npen = p.batch * (long long)O * S;
-  const long long pen = tile * W + w;
-  pc.active = pen < npen;
-  {
-    const long long pp = pc.active ? pen : 0;
-    const long long bo = pp / S;
-    pc.s = (int)(pp - bo * S);
-    pc.b = bo / O;
-    pc.o = (int)(bo - pc.b * O);
-  }
+  const bool turn = !COLS && !SPLIT && MOUT != MAP_IDENTITY && W > 1 && p.out.across;
+  const int PR = phys(L) + (turn && L >= 512 ? 32 / W : 0);
+  const int2* chain = !COLS && MOUT == MAP_NATURAL ? p.out.chain : nullptr;
+  int off = -1, unused = -1;   // position offset of the last stage (-1: none)
+  Pencil pc = pencil_at(p, tile * W + w, chain, unused);
   float2 v[P];
   {
     Addr<MIN> A;
@@ -326,26 +365,32 @@ __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int
   }
   float2 twb[8];
   if (p.st[0].Ns > 1)
-    LFFT_RADIX_SWITCH(p.st[0].radix, (prefetch_tw<P, RR>(twb, p.st[0], jt, TPP)));
+    LFFT_RADIX_SWITCH(p.st[0].radix, (prefetch_tw<P, RR>(twb, p.st[0], jt, TPP, -1)));
   for (int si = 0; si < p.nst; ++si) {
     const StageDesc& st = p.st[si];
     LFFT_RADIX_SWITCH(st.radix, (compute_stage<P, RR>(v, twb, p.sign, st.Ns > 1)));
     if (si + 1 < p.nst) {
       const StageDesc& nx = p.st[si + 1];
-      if (nx.Ns > 1) LFFT_RADIX_SWITCH(nx.radix, (prefetch_tw<P, RR>(twb, nx, jt, TPP)));
+      const int w0 = w, j0 = jt;
+      if (turn && si + 2 == p.nst) {
+        w = tid % W;
+        jt = tid / W;
+        pc = pencil_at(p, tile * W + w, chain, off);
+      }
+      if (nx.Ns > 1) LFFT_RADIX_SWITCH(nx.radix, (prefetch_tw<P, RR>(twb, nx, jt, TPP, off)));
       if constexpr (!SPLIT) {
-        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 0>(v, lds, st, jt, TPP, w, W, L)));
+        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 0>(v, lds, st, j0, TPP, w0, W, PR)));
         __syncthreads();
-        LFFT_RADIX_SWITCH(nx.radix, (lds_read<P, RR, COLS, 0>(v, lds, nx, jt, TPP, w, W, L)));
+        LFFT_RADIX_SWITCH(nx.radix, (lds_read<P, RR, COLS, 0>(v, lds, nx, jt, TPP, w, W, PR, off)));
         __syncthreads();
       } else {
-        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 1>(v, lds, st, jt, TPP, w, W, L)));
+        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 1>(v, lds, st, j0, TPP, w0, W, PR)));
         __syncthreads();
-        LFFT_RADIX_SWITCH(nx.radix, (lds_read<P, RR, COLS, 1>(v, lds, nx, jt, TPP, w, W, L)));
+        LFFT_RADIX_SWITCH(nx.radix, (lds_read<P, RR, COLS, 1>(v, lds, nx, jt, TPP, w, W, PR, off)));
         __syncthreads();
-        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 2>(v, lds, st, jt, TPP, w, W, L)));
+        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 2>(v, lds, st, j0, TPP, w0, W, PR)));
         __syncthreads();
-        LFFT_RADIX_SWITCH(nx.radix, (lds_read<P, RR, COLS, 2>(v, lds, nx, jt, TPP, w, W, L)));
+        LFFT_RADIX_SWITCH(nx.radix, (lds_read<P, RR, COLS, 2>(v, lds, nx, jt, TPP, w, W, PR, off)));
         __syncthreads();
       }
     }
@@ -353,7 +398,7 @@ __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int
   if (pc.active) {
     Addr<MOUT> A;
     addr_init<MOUT>(A, p.out, out, pc, L, S);
-    store_last<P, MOUT>(v, p, A, jt, TPP, pc);
+    store_last<P, MOUT>(v, p, A, jt, TPP, pc, off);
   }
 }
 

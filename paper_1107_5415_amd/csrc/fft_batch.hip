@@ -101,7 +101,7 @@ hipError_t set_attr() {
 
 }  // namespace
 
-size_t batch_lds_bytes(int tile) { return (size_t)(tile + tile / 16 + 1) * sizeof(float2); }
+size_t batch_lds_bytes(int tile) { return (size_t)(tile + tile / 16 + fastk::kTilePad) * sizeof(float2); }
 
 int batch_occupancy(int tile_lg) {
   if (tile_lg < 11 || tile_lg > 13 || set_attr() != hipSuccess) return 0;

@@ -219,6 +219,19 @@ __device__ __forceinline__ void gadd32(const MapDesc& m, int* c, int4 b) {
   }
 }
 
+// four-step twiddle exp(sign 2 pi i k lo / postN): k < post_lmod and
+// lo < lo_n, so the product stays below postN = post_lmod lo_n
+__device__ __forceinline__ float2 post_twiddle(const PassDesc& p, unsigned x) {
+  float2 w = c_mul(p.tw_hi[x >> 12], p.tw_lo[x & 4095]);
+  if (p.sign > 0) w.y = -w.y;
+  return w;
+}
+
+__device__ __forceinline__ unsigned post_lo(const PassDesc& p, int s) {
+  const unsigned q = fast_div((unsigned)s, p.f_lodiv);
+  return q - fast_div(q, p.f_lon) * (unsigned)p.lo_n;
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs of the MI355X.  Map
 // dispatch index i to a logical tile so that every XCD works on one
 // contiguous range of tiles: concurrently running neighbours share cache

@@ -47,7 +47,7 @@ hipError_t launch_t(const PassDesc& p, const float2* in, float2* out, hipStream_
   const long long tiles = (npen + p.W - 1) / p.W;
   const int nt = p.W * (p.L / P);
   const int tile = p.W * p.L;
-  const size_t lds = (size_t)(tile + tile / 16 + 1) * (SPLIT ? sizeof(float) : sizeof(float2));
+  const size_t lds = (size_t)(tile + tile / 16 + fastk::kTilePad) * (SPLIT ? sizeof(float) : sizeof(float2));
   hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(nt), lds, s, p, in, out);
   return hipGetLastError();
 }

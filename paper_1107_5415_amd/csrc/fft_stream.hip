@@ -347,20 +347,15 @@ __device__ __forceinline__ void store_tile(const float2* v, const PassDesc& p,
   side_init<MOUT>(A, p.out, out, t.b, o, s, L, p.S);
   float2* base = const_cast<float2*>(A.base);
   const bool scaled = p.scale != 1.0f;
+  const unsigned lo = p.post ? post_lo(p, s) : 0u;
 #pragma unroll
   for (int q = 0; q < kP / R; ++q) {
     const int j = jt + TPP * q;
     const int out0 = (j / Ns) * Ns * R + (j & (Ns - 1));
     side_positions<MOUT, R>(A, p.out, p.S, out0, Ns, [&](int i, int off) {
       float2 x = v[q * R + i];
-      if (p.post) {
-        const int l = (out0 + i * Ns) % p.post_lmod;
-        const long long lo = (s / p.lo_div) % p.lo_n;
-        const long long tt = ((long long)l * lo) % p.postN;
-        float2 wv = c_mul(p.tw_hi[tt >> 12], p.tw_lo[tt & 4095]);
-        if (p.sign > 0) wv.y = -wv.y;
-        x = c_mul(x, wv);
-      }
+      // (the pencil is one digit, the four-step axis's high one)
+      if (p.post) x = c_mul(x, post_twiddle(p, (unsigned)(out0 + i * Ns) * lo));
       if (scaled) {
         x.x *= p.scale;
         x.y *= p.scale;

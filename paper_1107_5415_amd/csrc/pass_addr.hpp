@@ -1,6 +1,5 @@
 // Addressing of a pass tile whose pencils may cross signals: which pencil a
-// tile's w-th one is, where its positions lie on either side, and the
-// four-step twiddle.  Used by the mixed-radix and the chirp-z kernels.
+// tile's w-th one is and where its positions lie on either side.  Used by the mixed-radix and the chirp-z kernels.
 #pragma once
 #include "fft_common.hpp"
 
@@ -106,19 +105,6 @@ __device__ __forceinline__ void offsets(const PassDesc& p, const MapDesc& m, con
       }
     }
   }
-}
-
-// four-step twiddle exp(sign 2 pi i k lo / postN): k < post_lmod and
-// lo < lo_n, so the product stays below postN = post_lmod lo_n
-__device__ __forceinline__ float2 post_twiddle(const PassDesc& p, unsigned x) {
-  float2 w = c_mul(dev_ptr(p.tw_hi)[x >> 12], dev_ptr(p.tw_lo)[x & 4095]);
-  if (p.sign > 0) w.y = -w.y;
-  return w;
-}
-
-__device__ __forceinline__ unsigned post_lo(const PassDesc& p, int s) {
-  const unsigned q = fast_div((unsigned)s, p.f_lodiv);
-  return q - fast_div(q, p.f_lon) * (unsigned)p.lo_n;
 }
 
 // position of l in the pencil's last digit

@@ -59,6 +59,13 @@ std::vector<int> nontrivial_axes(const Smith& S) {
   return t;
 }
 
+// the coordinate whose unit step is the step to the next natural index
+int last_side(const Mat& H) {
+  int i = H.d - 1;
+  while (i > 0 && H.a[i][i] == 1) --i;
+  return i;
+}
+
 // Sample side of basis S on lattice A: natural box of A, unit steps Q e_t.
 Side sample_side(const Smith& S, const Mat& A) {
   Side s;
@@ -68,6 +75,7 @@ Side sample_side(const Smith& S, const Mat& A) {
     Vec4 u = zero4();
     for (int i = 0; i < S.d; ++i) u[i] = S.Q.a[i][t];
     s.unit.push_back(reduce4(s.H, u));
+    s.next.push_back(posmod(S.Qinv.a[t][last_side(s.H)], S.eps[t]));
   }
   return s;
 }
@@ -81,6 +89,8 @@ Side freq_side(const Smith& S, const Mat& A) {
     Vec4 u = zero4();
     for (int i = 0; i < S.d; ++i) u[i] = S.R.a[t][i];
     s.unit.push_back(reduce4(s.H, u));
+    // mu = R^{-T} h
+    s.next.push_back(posmod(S.Rinv.a[last_side(s.H)][t], S.eps[t]));
   }
   return s;
 }
@@ -442,6 +452,44 @@ MapDesc identity_map(bool across) {
   return m;
 }
 
+// Rows of the last pass (digits [0, a) x one digit of length n) in chains of
+// W natural neighbours, see MapDesc::chain: the step to the next natural
+// index moves row and position by fixed amounts, so the rows fall into cycles
+// of one length, cut into chains of W.  Empty if that step stays in its row
+// or the cycles are shorter than W.
+std::vector<int2> row_chains(const Side& side, const std::vector<i64>& eps,
+                             const std::vector<Digit>& dg, int a, int W) {
+  std::vector<int2> out;
+  const i64 O = range_count(dg, 0, a), L = dg[a].n;
+  std::vector<i64> mu(eps.size());
+  auto place = [&](i64& row) {     // row and position of grid coordinates mu
+    row = 0;
+    for (int g = 0; g < a; ++g) row = row * dg[g].n + (mu[dg[g].axis] / dg[g].w_out) % dg[g].n;
+    return (mu[dg[a].axis] / dg[a].w_out) % L;
+  };
+  std::vector<char> seen(O, 0);
+  for (i64 first = 0; first < O; ++first) {
+    if (seen[first]) continue;
+    std::fill(mu.begin(), mu.end(), 0);
+    i64 r = first;
+    for (int g = a - 1; g >= 0; --g) {
+      mu[dg[g].axis] += (r % dg[g].n) * dg[g].w_out;
+      r /= dg[g].n;
+    }
+    i64 row = first, pos = 0, start = 0, len = 0;
+    do {
+      if (len % W == 0) start = pos;
+      seen[row] = 1;
+      out.push_back(make_int2((int)row, (int)posmod(pos - start, L)));
+      ++len;
+      for (size_t t = 0; t < eps.size(); ++t) mu[t] = (mu[t] + side.next[t]) % eps[t];
+      pos = place(row);
+    } while (row != first);
+    if (len < W || len % W != 0) return {};
+  }
+  return out;
+}
+
 // Schedule for fixed tiles of T = 2^tile_lg elements (the batched persistent
 // launch): every pass is one power-of-two pencil of 32..T points, so every
 // pass runs the register-resident kernel with W = T / L pencils per tile.
@@ -540,7 +588,7 @@ void mixed_shape(const LatticePlan* p, PassDesc& pd) {
   pd.f_TP = make_fast_div(pd.TP);
 }
 
-// index divisions of the kernels whose tiles cross signals
+// index divisions
 void pass_divisions(const LatticePlan* p, PassDesc& pd) {
   pd.wide = p->m >= (i64(1) << 30) ? 1 : 0;
   pd.f_S = make_fast_div(pd.S);
@@ -577,17 +625,23 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
       pd.split = 0;
     } else if (pow2) {
       pd.kind = 1;
+      // the last rows of a four-step axis: register-resident kernel, at least
+      // four rows per tile (see row_chains)
+      const bool four_step = pi > 0 && pi == np - 1 && pd.S == 1 && dg[R.a].part == 2;
       if (pd.S == 1) {
         pd.P = 16;
-        pd.W = (int)std::max<i64>(1, 4096 / pd.L);
+        pd.W = (int)std::max<i64>(four_step ? std::min<i64>(4, 16384 / pd.L) : 1, 4096 / pd.L);
         pd.split = 0;
       } else {
         // widest column tile that divides S and fits 16384 elements; passes
         // with fewer than 512 such tiles get narrower tiles (down to 8
         // columns, whole 64-byte segments) so that every CU has work
         const i64 npen = batch_pencils(p, pd);
+        // (several digits: 8192 elements where that leaves 8 columns, so that
+        // two workgroups share a CU: (64, 2^16) 216 -> 186 us over 2^22 points)
         int Wc = 64;
         while (Wc > 1 && (pd.S % Wc != 0 || (i64)Wc * pd.L > 16384)) Wc /= 2;
+        while (Wc > 8 && R.b - R.a > 1 && (i64)Wc * pd.L > 8192) Wc /= 2;
         while (Wc > 8 && npen / Wc < 512) Wc /= 2;
         pd.W = Wc;
         pd.P = 16;
@@ -596,7 +650,7 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
       if ((i64)pd.W * pd.L / pd.P > 1024) pd.kind = 0;
       // the streaming kernel assumes full tiles inside one signal and
       // 32-bit element offsets
-      if (pd.kind == 1 && R.b - R.a == 1 && stream_supported(pd.L, pd.W, pd.S > 1) &&
+      if (pd.kind == 1 && !four_step && R.b - R.a == 1 && stream_supported(pd.L, pd.W, pd.S > 1) &&
           ((i64)pd.O * pd.S) % pd.W == 0 && p->m < (i64(1) << 28))
         pd.kind = 2;
     }
@@ -673,7 +727,7 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
       pd.tw_lo = pr.second;
     }
     if (pd.kind == 0) mixed_shape(p, pd);
-    if (pd.kind == 0 || pd.kind >= 4) pass_divisions(p, pd);
+    pass_divisions(p, pd);
     pd.in = identity_map(pd.S > 1);
     pd.out = identity_map(pd.S > 1);
     E.passes.push_back(pd);
@@ -687,7 +741,8 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
   if (any_split) {
     MapDesc m{};
     m.mode = MAP_LINEAR;
-    m.across = E.passes.back().S > 1 ? 1 : 0;
+    // (the high digit's outputs are consecutive)
+    m.across = 1;
     m.To = p->blob.ref(linear_table(p->eps, dg, 0, R1.a));
     m.Tl = p->blob.ref(linear_table(p->eps, dg, R1.a, R1.b));
     m.Ts = p->blob.ref(linear_table(p->eps, dg, R1.b, D));
@@ -697,6 +752,14 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
   }
   E.out_nat = natural_map(p->blob, out_side, p->d, dg, R1.a, R1.b, true);
   E.has_nat_out = true;
+  const PassDesc& end = E.passes.back();
+  if (end.kind == 1 && end.S == 1 && end.W > 1 && R1.b - R1.a == 1 && R1.a > 0 && !end.post) {
+    const std::vector<int2> chain = row_chains(out_side, p->eps, dg, R1.a, end.W);
+    if (!chain.empty()) {
+      E.out_nat.chain = p->blob.ref(chain);
+      E.out_nat.across = 1;
+    }
+  }
 }
 
 template <class T>
@@ -708,6 +771,7 @@ void patch_map(MapDesc& m, uintptr_t base) {
   patch(m.To, base);
   patch(m.Tl, base);
   patch(m.Ts, base);
+  patch(m.chain, base);
 }
 
 void patch_engine(Engine& E, uintptr_t base) {
@@ -808,12 +872,19 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
             p->digits.push_back(Digit{j, n, 3, 1, 1});
             continue;
           }
-          // power-of-two axes: a high digit of at least 32 points, so that
-          // both passes run the register-resident kernels (2^15 = 32 x 1024
-          // rather than 4 x 8192; 1.7-2.3 times faster on 2^14 .. 2^17
-          // cycles).  Not beyond the streaming kernels' 2^28 bound, where the
+          // power-of-two axes: rows of 4096 points (2048 below 2^22), four of
+          // which fit a tile of the register-resident kernel and come out as
+          // runs of natural neighbours (row_chains): 2^22 points of the cycle
+          // in [[2048, 8], [0, 2048]] took 91 us with rows of 8192, 52 us with
+          // 4096, 59 with 2048; 8 x 2^20 126, 111 and 99 us.  The high digit
+          // has at least 32 points, so that both passes run the register
+          // kernels.  Not beyond the streaming kernels' 2^28 bound, where the
           // wider low digit measured faster overall.
-          if (is_pow2(n) && n / lo < 32 && n >= 32 * 32 && p->m < (i64(1) << 28)) lo = n / 32;
+          if (is_pow2(n) && n >= 32 * 32 && p->m < (i64(1) << 28)) {
+            const i64 rows = p->m >= (i64(1) << 22) ? 4096 : 2048;
+            if (n / rows <= kMaxPencil) lo = std::min(lo, rows);
+            if (n / lo < 32) lo = n / 32;
+          }
           i64 hi = n / lo;
           p->digits.push_back(Digit{j, hi, 1, lo, 1});
           p->digits.push_back(Digit{j, lo, 2, 1, hi});

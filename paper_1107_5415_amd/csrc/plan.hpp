@@ -41,6 +41,7 @@ using Vec4 = std::array<i64, 4>;
 struct Side {
   Mat H;                    // column Hermite form (upper triangular)
   std::vector<Vec4> unit;   // reduced natural coordinates, one per grid axis
+  std::vector<i64> next;    // grid coordinates of the step to the next natural index
 };
 
 struct Digit {
