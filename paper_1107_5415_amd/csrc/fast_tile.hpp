@@ -334,7 +334,7 @@ __device__ __forceinline__ Pencil pencil_at(const PassDesc& p, long long pen, co
 // neighbouring threads on neighbouring rows, each row turned by the position
 // of its neighbour, so that a wave writes runs of W elements.  The change of
 // thread order rides on the last LDS exchange and the turn on the twiddles,
-// so neither costs anything.  The rows' LDS pitch is 32 / W elements modulo
+// so neither costs anything.  Column tiles only reorder their own columns.  The rows' LDS pitch is 32 / W elements modulo
 // 32 then, which spreads those reads over all banks.
 constexpr int kTilePad = 33;
 
@@ -356,6 +356,12 @@ __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int
   const int PR = phys(L) + (turn && L >= 512 ? 32 / W : 0);
   const int2* chain = !COLS && MOUT == MAP_NATURAL ? p.out.chain : nullptr;
   int off = -1, unused = -1;   // position offset of the last stage (-1: none)
+  int off_cols = -1;
+  if (COLS && MOUT == MAP_NATURAL && p.out.chain) {
+    const int2 c = p.out.chain[w];
+    w = c.x;
+    off_cols = c.y;
+  }
   Pencil pc = pencil_at(p, tile * W + w, chain, unused);
   float2 v[P];
   {
@@ -372,6 +378,7 @@ __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int
     if (si + 1 < p.nst) {
       const StageDesc& nx = p.st[si + 1];
       const int w0 = w, j0 = jt;
+      if (COLS && si + 2 == p.nst) off = off_cols;
       if (turn && si + 2 == p.nst) {
         w = tid % W;
         jt = tid / W;

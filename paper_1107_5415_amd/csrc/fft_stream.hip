@@ -187,8 +187,16 @@ __device__ __forceinline__ void load_tile(float2* v, const PassDesc& p, const fl
   }
 }
 
+// The last stage can be turned: with p = (j + off) mod L in the place of its
+// butterfly index j, the inputs of butterfly p mod Ns and the twiddles of
+// exponent p give the outputs p, p + Ns, ... mod L (off = 0: the plain stage).
 template <int L, int SI>
-__device__ __forceinline__ void tw_load(float2* twb, const PassDesc& p, int jt) {
+__device__ __forceinline__ int turned(int j, int off) {
+  return SI + 1 == NStages<L>::value ? (j + off) & (L - 1) : j;
+}
+
+template <int L, int SI>
+__device__ __forceinline__ void tw_load(float2* twb, const PassDesc& p, int jt, int off) {
   constexpr int R = StageR<L, SI>::value;
   constexpr int Ns = StageNs<L, SI>::value;
   constexpr int LG = Lg<R>::value;
@@ -196,10 +204,15 @@ __device__ __forceinline__ void tw_load(float2* twb, const PassDesc& p, int jt) 
   const float2* tw = p.st[0].tw;   // exp(-2 pi i k / L)
 #pragma unroll
   for (int q = 0; q < kP / R; ++q) {
-    const int j = jt + TPP * q;
-    const int tstep = (j & (Ns - 1)) * (L / (Ns * R));
+    const int j = turned<L, SI>(jt + TPP * q, off);
+    if constexpr (Ns * R == L) {
 #pragma unroll
-    for (int k = 0; k < LG; ++k) twb[q * LG + k] = tw[tstep << k];
+      for (int k = 0; k < LG; ++k) twb[q * LG + k] = tw[(j << k) & (L - 1)];
+    } else {
+      const int tstep = (j & (Ns - 1)) * (L / (Ns * R));
+#pragma unroll
+      for (int k = 0; k < LG; ++k) twb[q * LG + k] = tw[tstep << k];
+    }
   }
 }
 
@@ -286,13 +299,13 @@ __device__ __forceinline__ void exch_write(const float2* v, void* lds, int jt, i
 }
 
 template <int L, int W, bool COLS, int SI, int PART>
-__device__ __forceinline__ void exch_read(float2* v, const void* lds, int jt, int w) {
+__device__ __forceinline__ void exch_read(float2* v, const void* lds, int jt, int w, int off) {
   constexpr int R = StageR<L, SI>::value;
   constexpr int TPP = L / kP;
   static_assert((L / R) % 16 == 0, "read stride must keep LDS offsets linear");
 #pragma unroll
   for (int q = 0; q < kP / R; ++q) {
-    const int j = jt + TPP * q;
+    const int j = turned<L, SI>(jt + TPP * q, off) & (L / R - 1);
     const int eb = slds<COLS, L, W>(j, w);
 #pragma unroll
     for (int i = 0; i < R; ++i) {
@@ -309,34 +322,34 @@ __device__ __forceinline__ void exch_read(float2* v, const void* lds, int jt, in
 
 template <int L, int W, bool COLS, bool SPLIT, int SI>
 __device__ __forceinline__ void stages_from(float2* v, float2* twb, void* lds, const PassDesc& p,
-                                            int jt, int w) {
+                                            int jt, int w, int off) {
   constexpr int NS = NStages<L>::value;
   stage_compute<L, SI>(v, twb, p.sign);
   if constexpr (SI + 1 < NS) {
-    tw_load<L, SI + 1>(twb, p, jt);
+    tw_load<L, SI + 1>(twb, p, jt, off);
     if constexpr (!SPLIT) {
       exch_write<L, W, COLS, SI, 0>(v, lds, jt, w);
       __syncthreads();
-      exch_read<L, W, COLS, SI + 1, 0>(v, lds, jt, w);
+      exch_read<L, W, COLS, SI + 1, 0>(v, lds, jt, w, off);
       __syncthreads();
     } else {
       exch_write<L, W, COLS, SI, 1>(v, lds, jt, w);
       __syncthreads();
-      exch_read<L, W, COLS, SI + 1, 1>(v, lds, jt, w);
+      exch_read<L, W, COLS, SI + 1, 1>(v, lds, jt, w, off);
       __syncthreads();
       exch_write<L, W, COLS, SI, 2>(v, lds, jt, w);
       __syncthreads();
-      exch_read<L, W, COLS, SI + 1, 2>(v, lds, jt, w);
+      exch_read<L, W, COLS, SI + 1, 2>(v, lds, jt, w, off);
       __syncthreads();
     }
-    stages_from<L, W, COLS, SPLIT, SI + 1>(v, twb, lds, p, jt, w);
+    stages_from<L, W, COLS, SPLIT, SI + 1>(v, twb, lds, p, jt, w, off);
   }
 }
 
 template <int L, bool COLS, int MOUT>
 __device__ __forceinline__ void store_tile(const float2* v, const PassDesc& p,
                                            float2* __restrict__ out, const TileId& t, int w,
-                                           int jt) {
+                                           int jt, int off) {
   constexpr int NS = NStages<L>::value;
   constexpr int R = StageR<L, NS - 1>::value;
   constexpr int Ns = StageNs<L, NS - 1>::value;
@@ -350,8 +363,7 @@ __device__ __forceinline__ void store_tile(const float2* v, const PassDesc& p,
   const unsigned lo = p.post ? post_lo(p, s) : 0u;
 #pragma unroll
   for (int q = 0; q < kP / R; ++q) {
-    const int j = jt + TPP * q;
-    const int out0 = (j / Ns) * Ns * R + (j & (Ns - 1));
+    const int out0 = turned<L, NS - 1>(jt + TPP * q, off);
     side_positions<MOUT, R>(A, p.out, p.S, out0, Ns, [&](int i, int off) {
       float2 x = v[q * R + i];
       // (the pencil is one digit, the four-step axis's high one)
@@ -383,8 +395,18 @@ __global__ void __launch_bounds__(W * L / kP, (COLS ? kColsWgPerCu : kRowsWgPerC
   void* lds = lds_raw;
   constexpr int TPP = L / kP;
   const int tid = threadIdx.x;
-  const int w = COLS ? tid % W : tid / TPP;
+  int w = COLS ? tid % W : tid / TPP;
   const int jt = COLS ? tid / W : tid % TPP;
+  // columns in the order of natural neighbours (MapDesc::chain): the lanes of
+  // a tile row still read the same segment, and they write runs
+  int off = 0;
+  if constexpr (COLS && MOUT == MAP_NATURAL) {
+    if (p.out.chain) {
+      const int2 c = p.out.chain[w];
+      w = c.x;
+      off = c.y;
+    }
+  }
   const long long npen = p.batch * (long long)p.O * p.S;
   const long long ntiles = npen / W;
   // persistent schedule: XCD x owns tiles [beg_x, end_x); its k-th workgroup
@@ -403,8 +425,8 @@ __global__ void __launch_bounds__(W * L / kP, (COLS ? kColsWgPerCu : kRowsWgPerC
   for (; tile < end; tile += nwg_x) {
     const TileId ta = tile_of<W>(tile, p.O, p.S);
     load_tile<L, COLS, MIN>(va, p, in, ta, w, jt);
-    stages_from<L, W, COLS, SPLIT, 0>(va, twb, lds, p, jt, w);
-    store_tile<L, COLS, MOUT>(va, p, out, ta, w, jt);
+    stages_from<L, W, COLS, SPLIT, 0>(va, twb, lds, p, jt, w, off);
+    store_tile<L, COLS, MOUT>(va, p, out, ta, w, jt, off);
   }
 }
 

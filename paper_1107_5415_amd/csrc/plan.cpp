@@ -490,6 +490,30 @@ std::vector<int2> row_chains(const Side& side, const std::vector<i64>& eps,
   return out;
 }
 
+// The W columns of a tile of the last pass (the digit a whole, others after
+// it) in runs of natural neighbours, see MapDesc::chain: the step to the next
+// natural index moves c columns and a fixed number of positions.  Empty
+// unless 0 < |c| < W.
+std::vector<int2> column_chain(const Side& side, const std::vector<i64>& eps,
+                               const std::vector<Digit>& dg, int a, int W) {
+  const int D = (int)dg.size(), end = dg[D - 1].axis;
+  if (dg[a].part != 0 || dg[D - 1].part != 0) return {};
+  for (size_t t = 0; t < eps.size(); ++t)
+    if ((int)t != dg[a].axis && (int)t != end && side.next[t] != 0) return {};
+  i64 c = side.next[end];
+  if (2 * c > eps[end]) c -= eps[end];
+  const i64 k = c < 0 ? -c : c;
+  if (k == 0 || k >= W) return {};
+  std::vector<int2> out;
+  for (i64 r = 0; r < k; ++r) {
+    const i64 n = (W - r + k - 1) / k;   // columns r, r + k, ...
+    for (i64 i = 0; i < n; ++i)
+      out.push_back(make_int2((int)(r + k * (c > 0 ? i : n - 1 - i)),
+                              (int)((i * side.next[dg[a].axis]) % dg[a].n)));
+  }
+  return out;
+}
+
 // Schedule for fixed tiles of T = 2^tile_lg elements (the batched persistent
 // launch): every pass is one power-of-two pencil of 32..T points, so every
 // pass runs the register-resident kernel with W = T / L pencils per tile.
@@ -759,6 +783,10 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
       E.out_nat.chain = p->blob.ref(chain);
       E.out_nat.across = 1;
     }
+  }
+  if ((end.kind == 1 || end.kind == 2) && end.S > 1 && R1.b - R1.a == 1 && !end.post) {
+    const std::vector<int2> chain = column_chain(out_side, p->eps, dg, R1.a, end.W);
+    if (!chain.empty()) E.out_nat.chain = p->blob.ref(chain);
   }
 }
 
