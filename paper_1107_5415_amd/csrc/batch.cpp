@@ -59,8 +59,13 @@ void* upload(const std::vector<T>& v) {
 
 // Fill the eight XCD queues of both phases of one direction: phase 0 holds
 // the first pass of every lattice, phase 1 the second pass of the lattices
-// that need two.  Lattices go to queues by longest-processing-time
-// assignment, largest first inside a queue.
+// that need two.  The tiles of a phase, largest lattice first, go to the
+// queues in runs of at most 1/128 of them, each to the shortest queue: every
+// XCD gets the same number of tiles (all of one size) of the same mix, and
+// neighbouring tiles of a lattice share an L2.  (Whole lattices: the pyramids'
+// nine channels left most XCDs idle, 912 -> 1242 us over 2^24 points; the
+// plain order cut into eight: 403 -> 418 us for 512 lattices, whose large ones
+// cost more per tile.)
 void build_dir(BatchPlan* b, bool inverse, BatchDir& D) {
   std::vector<BatchPass> passes;
   struct Inst {
@@ -107,27 +112,31 @@ void build_dir(BatchPlan* b, bool inverse, BatchDir& D) {
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(),
                    [&](int x, int y) { return insts[x].work > insts[y].work; });
-  std::vector<std::vector<int>> q(8);
-  std::vector<i64> load(8, 0);
-  for (int k : order) {
-    int best = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-    q[best].push_back(k);
-    load[best] += insts[k].work;
-  }
   std::vector<int2> items;
   std::vector<int> qbeg(17, 0);
   for (int ph = 0; ph < 2; ++ph) {
-    for (int x = 0; x < 8; ++x) {
-      qbeg[8 * ph + x] = (int)items.size();
-      for (int k : q[x]) {
-        const Inst& I = insts[k];
-        if (ph >= I.np) continue;
-        const int pi = I.first + ph;
-        const i64 nt = pass_tiles(passes[pi].pd);
-        for (i64 t = 0; t < nt; ++t) items.push_back(make_int2(pi, (int)t));
+    i64 total = 0;
+    for (const Inst& I : insts)
+      if (ph < I.np) total += pass_tiles(passes[I.first + ph].pd);
+    const i64 run = std::max<i64>(4, total / 128);
+    std::vector<std::vector<int2>> q(8);
+    for (int k : order) {
+      const Inst& I = insts[k];
+      if (ph >= I.np) continue;
+      const int pi = I.first + ph;
+      const i64 nt = pass_tiles(passes[pi].pd);
+      for (i64 t = 0; t < nt; t += run) {
+        auto& dst = *std::min_element(q.begin(), q.end(), [](const auto& x, const auto& y) {
+          return x.size() < y.size();
+        });
+        for (i64 u = t; u < std::min(nt, t + run); ++u) dst.push_back(make_int2(pi, (int)u));
       }
     }
-    D.phase_items[ph] = (int)items.size() - qbeg[8 * ph];
+    D.phase_items[ph] = (int)total;
+    for (int x = 0; x < 8; ++x) {
+      qbeg[8 * ph + x] = (int)items.size();
+      items.insert(items.end(), q[x].begin(), q[x].end());
+    }
   }
   qbeg[16] = (int)items.size();
   if (items.size() > (size_t)0x7fffffff) throw StatusError{E_UNSUPPORTED};
@@ -166,8 +175,6 @@ void enqueue_persistent(BatchPlan* b, bool inverse, const void* in, void* out, v
                         hipStream_t s, bool trace) {
   const BatchDir& D = b->dir[inverse ? 1 : 0];
   if (D.nitems > 0) {
-    hipError_t e = launch_batch_clear(b->dheads, 16, s);
-    if (e != hipSuccess) throw StatusError{E_HIP};
     for (int ph = 0; ph < 2; ++ph) {
       if (D.phase_items[ph] == 0) continue;
       // method bytes: 16 B per point of every lattice with a pass in this
@@ -183,13 +190,11 @@ void enqueue_persistent(BatchPlan* b, bool inverse, const void* in, void* out, v
       }
       TraceScope ts(trace && trace_on() ? batch_kernel_name(b->tile_lg) : nullptr, bytes,
                     pass_bytes, s);
-      // never more workgroups than items: idle ones would only contend for
-      // the queue heads
       const int grid = std::min(b->grid, std::max(8, D.phase_items[ph]));
-      e = launch_batch(b->tile_lg, static_cast<const BatchPass*>(D.dpass),
+      const hipError_t e = launch_batch(b->tile_lg, static_cast<const BatchPass*>(D.dpass),
                        static_cast<const int2*>(D.ditems), D.qbeg + 8 * ph,
-                       b->dheads + 8 * kHeadStride * ph, static_cast<const float2*>(in),
-                       static_cast<float2*>(out), static_cast<float2*>(ws), grid, s);
+                       static_cast<const float2*>(in), static_cast<float2*>(out),
+                       static_cast<float2*>(ws), grid, s);
       if (e != hipSuccess) throw StatusError{E_HIP};
     }
   }
@@ -255,9 +260,6 @@ BatchPlan* build_batch_plan_at(int count, int d, const i64* Ms, const i64* in_of
     }
     if (b->extra_ws && in_off) throw StatusError{E_UNSUPPORTED};
     if (!(flags & kPlanHostOnly)) {
-      const size_t n = 16 * kHeadStride * sizeof(int);
-      if (hipMalloc(&b->dheads, n) != hipSuccess) throw StatusError{E_NOMEM};
-      if (hipMemset(b->dheads, 0, n) != hipSuccess) throw StatusError{E_HIP};
       if (hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess)
         throw StatusError{E_HIP};
     }
@@ -273,7 +275,6 @@ void free_batch_plan(BatchPlan* b) {
   if (!b) return;
   drop_tiled(b);
   for (auto* p : b->single) free_plan(p);
-  if (b->dheads) (void)hipFree(b->dheads);
   if (b->cap) (void)hipStreamDestroy(b->cap);
   delete b;
 }
@@ -314,7 +315,7 @@ void configure_batch(BatchPlan* b, int tile_lg, int order) {
 
 void exec_batch(BatchPlan* b, bool inverse, int mode, const void* in, void* out, void* ws,
                 hipStream_t s) {
-  if (!b->configured || !b->dheads) throw StatusError{E_STATE};
+  if (!b->configured || (b->flags & kPlanHostOnly)) throw StatusError{E_STATE};
   if (mode == BATCH_LOOP) {
     for (int i = 0; i < b->count; ++i) {
       LatticePlan* p = single_plan(b, i);
@@ -360,7 +361,7 @@ void exec_batch(BatchPlan* b, bool inverse, int mode, const void* in, void* out,
 
 void tune_batch(BatchPlan* b, const void* in, void* out, void* ws, int reps, hipStream_t s,
                 float* best_ms) {
-  if (!b->dheads || reps < 1) throw StatusError{E_ARG};
+  if ((b->flags & kPlanHostOnly) || reps < 1) throw StatusError{E_ARG};
   TuneKey key;
   key.arch = device_arch();
   key.d = b->d;

@@ -39,7 +39,6 @@ struct BatchPlan {
   std::vector<LatticePlan*> single;     // default plans, built on first per-lattice use
   int eligible = 0;
   BatchDir dir[2];                      // forward, inverse
-  int* dheads = nullptr;                // 16 queue heads (8 per phase), kHeadStride apart
   int grid = 0;
   hipStream_t cap = nullptr;            // private stream for graph capture
   std::map<std::tuple<int, const void*, void*, void*>, hipGraphExec_t> graphs;

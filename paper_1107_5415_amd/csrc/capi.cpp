@@ -411,7 +411,7 @@ int lfft_batch_schedule(lfft_batch_t plan, int i, int* passes, int64_t* pencil, 
 int lfft_batch_tune(lfft_batch_t plan, const void* in, void* out, void* workspace, int reps,
                     float* best_ms, hipStream_t stream) {
   if (!plan || !in || !out || in == out || !workspace || reps < 1) return LFFT_E_ARG;
-  if (!plan->b->dheads) return LFFT_E_STATE;
+  if (plan->b->flags & lfft::kPlanHostOnly) return LFFT_E_STATE;
   return guarded([&] {
     lfft::tune_batch(plan->b, in, out, workspace, reps, stream, best_ms);
     lfft::log_batch_plan(plan->b, "batch tuned:");
@@ -442,7 +442,7 @@ int lfft_batch_execute(lfft_batch_t plan, int inverse, int mode, const void* in,
                        void* workspace, hipStream_t stream) {
   if (!plan || !in || !out || in == out || !workspace) return LFFT_E_ARG;
   if (mode < LFFT_BATCH_LOOP || mode > LFFT_BATCH_GRAPH) return LFFT_E_ARG;
-  if (!plan->b->dheads) return LFFT_E_STATE;
+  if (plan->b->flags & lfft::kPlanHostOnly) return LFFT_E_STATE;
   return guarded([&] { lfft::exec_batch(plan->b, inverse != 0, mode, in, out, workspace, stream); });
 }
 

@@ -225,22 +225,37 @@ __device__ __forceinline__ int lds_e(int l, int w, int W, int PR) {
   return COLS ? phys(l * W + w) : w * PR + phys(l);
 }
 
+// Visit the LDS elements of positions l0 + i step, i < R.  The padding keeps
+// them an arithmetic progression when a step moves by whole 16-element groups
+// or when the R positions lie within one (a first stage's outputs, R of them
+// from a multiple of R): one addition per element then.
+template <int R, bool COLS, class F>
+__device__ __forceinline__ void for_lds(int l0, int step, int w, int W, int PR, F&& f) {
+  const int d = COLS ? step * W : step;
+  if ((d & 15) == 0 || (!COLS && step == 1)) {
+    const int e0 = lds_e<COLS>(l0, w, W, PR), de = d + (d >> 4);
+#pragma unroll
+    for (int i = 0; i < R; ++i) f(i, e0 + i * de);
+  } else {
+#pragma unroll
+    for (int i = 0; i < R; ++i) f(i, lds_e<COLS>(l0 + i * step, w, W, PR));
+  }
+}
+
 template <int P, int R, bool COLS, int PART>
 __device__ __forceinline__ void lds_write(const float2* v, void* lds, const StageDesc& st, int jt,
                                           int TPP, int w, int W, int PR) {
 #pragma unroll
   for (int q = 0; q < P / R; ++q) {
-    BfGeom g = geom(st, jt + TPP * q);
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      int e = lds_e<COLS>(g.out0 + i * g.out_step, w, W, PR);
+    const BfGeom g = geom(st, jt + TPP * q);
+    for_lds<R, COLS>(g.out0, g.out_step, w, W, PR, [&](int i, int e) {
       if constexpr (PART == 0)
         static_cast<float2*>(lds)[e] = v[q * R + i];
       else if constexpr (PART == 1)
         static_cast<float*>(lds)[e] = v[q * R + i].x;
       else
         static_cast<float*>(lds)[e] = v[q * R + i].y;
-    }
+    });
   }
 }
 
@@ -250,16 +265,14 @@ __device__ __forceinline__ void lds_read(float2* v, const void* lds, const Stage
 #pragma unroll
   for (int q = 0; q < P / R; ++q) {
     const BfGeom g = off < 0 ? geom(st, jt + TPP * q) : geom_turned(st, jt + TPP * q, off);
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      int e = lds_e<COLS>(g.in0 + i * g.in_step, w, W, PR);
+    for_lds<R, COLS>(g.in0, g.in_step, w, W, PR, [&](int i, int e) {
       if constexpr (PART == 0)
         v[q * R + i] = static_cast<const float2*>(lds)[e];
       else if constexpr (PART == 1)
         v[q * R + i].x = static_cast<const float*>(lds)[e];
       else
         v[q * R + i].y = static_cast<const float*>(lds)[e];
-    }
+    });
   }
 }
 

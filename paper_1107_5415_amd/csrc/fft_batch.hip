@@ -8,9 +8,12 @@
 // The kernel boundary between the phases orders the two passes of every
 // lattice, so the tiles need no counters, fences or waits.
 //
-// A workgroup takes items from the queue of its own XCD (dispatch index
-// mod 8) and, once that is empty, from the others; it exits when all eight
-// are empty.
+// A workgroup takes every n-th item of the queue of its own XCD (dispatch index
+// mod 8, n workgroups there).  All items are tiles of one size, so fixed
+// strides come within 1% of queue heads on 512 lattices of 2^10 .. 2^18 points
+// (408 against 403 us), without the atomic, the broadcast through LDS, the
+// launch that cleared the heads (a 512 x 512 picture's pyramid 118 -> 102 us)
+// and a state that two calls of one plan would share.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -23,39 +26,24 @@ namespace {
 using namespace dev;
 
 // blockDim.x = T / 16 threads (128, 256 or 512) for tiles of T elements.
-// qbeg[0..8]: queue boundaries of this phase; heads[32 q]: head of queue q
-// (one 128-byte line per head, so claims on different queues do not
-// serialise on one line).
+// qbeg[0..8]: queue boundaries of this phase.
 __global__ void __launch_bounds__(512) fft_batch_kernel(const BatchPass* __restrict__ passes,
                                                         const int2* __restrict__ items,
-                                                        const int* __restrict__ qbeg, int* heads,
+                                                        const int* __restrict__ qbeg,
                                                         const float2* in, float2* out,
                                                         float2* ws) {
   extern __shared__ float2 lds_raw[];
-  __shared__ int s_item;
   const int tid = threadIdx.x;
-  const int q0 = blockIdx.x & 7;
-  int tried = 0;  // queues found empty (thread 0)
-  for (;;) {
-    if (tid == 0) {
-      int it = -1;
-      while (tried < 8) {
-        const int q = (q0 + tried) & 7;
-        const int k = atomicAdd(&heads[kHeadStride * q], 1);
-        if (qbeg[q] + k < qbeg[q + 1]) {
-          it = qbeg[q] + k;
-          break;
-        }
-        ++tried;
-      }
-      s_item = it;
-    }
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(s_item);
-    if (it < 0) break;
-    const int2 I = items[it];
-    const int pi = __builtin_amdgcn_readfirstlane(I.x);
-    const long long tile = __builtin_amdgcn_readfirstlane(I.y);
+  const int q = blockIdx.x & 7;
+  const int end = qbeg[q + 1], step = ((int)gridDim.x + 7 - q) >> 3;
+  int it = qbeg[q] + (int)(blockIdx.x >> 3);
+  if (it >= end) return;
+  int2 next = items[it];
+  for (; it < end; it += step) {
+    const int pi = __builtin_amdgcn_readfirstlane(next.x);
+    const long long tile = __builtin_amdgcn_readfirstlane(next.y);
+    // the next item while this one runs
+    if (it + step < end) next = items[it + step];
     const BatchPass& bp = passes[pi];
     const float2* src = (bp.in_buf == 0 ? in : bp.in_buf == 1 ? out : ws) + bp.in_off;
     float2* dst = (bp.out_buf == 1 ? out : ws) + bp.out_off;
@@ -76,22 +64,15 @@ __global__ void __launch_bounds__(512) fft_batch_kernel(const BatchPass* __restr
         fastk::fast_tile<16, true, false, MAP_IDENTITY, MAP_NATURAL>(bp.pd, tile, tid, src, dst, lds_raw);
         break;
     }
-    __syncthreads();
+    // (a tile ends with a barrier after its last LDS read, so the next one
+    // may write)
   }
-}
-
-// Zero the queue heads (a kernel rather than a memset so that the launch can
-// be captured into a graph).
-__global__ void __launch_bounds__(64) batch_clear_kernel(int* heads, int n) {
-  const int i = threadIdx.x;
-  if (i < n) heads[kHeadStride * i] = 0;
 }
 
 std::atomic<bool> g_attr{false};
 
 hipError_t set_attr() {
   if (g_attr.load(std::memory_order_acquire)) return hipSuccess;
-  // the dynamic size requested exactly: the kernel also has static LDS
   hipError_t e = hipFuncSetAttribute((const void*)fft_batch_kernel,
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)batch_lds_bytes(1 << 13));
@@ -114,20 +95,13 @@ int batch_occupancy(int tile_lg) {
 
 const char* batch_kernel_name(int) { return "fft_batch_kernel"; }
 
-hipError_t launch_batch_clear(int* heads, int n, hipStream_t s) {
-  if (n < 1 || n > 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(batch_clear_kernel, dim3(1), dim3(64), 0, s, heads, n);
-  return hipGetLastError();
-}
-
 hipError_t launch_batch(int tile_lg, const BatchPass* passes, const int2* items, const int* qbeg,
-                        int* heads, const float2* in, float2* out, float2* ws, int grid,
-                        hipStream_t s) {
-  if (tile_lg < 11 || tile_lg > 13) return hipErrorInvalidValue;
+                        const float2* in, float2* out, float2* ws, int grid, hipStream_t s) {
+  if (tile_lg < 11 || tile_lg > 13 || grid < 8) return hipErrorInvalidValue;  // every queue
   hipError_t e = set_attr();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fft_batch_kernel, dim3(grid), dim3(1 << (tile_lg - 4)),
-                     batch_lds_bytes(1 << tile_lg), s, passes, items, qbeg, heads, in, out, ws);
+                     batch_lds_bytes(1 << tile_lg), s, passes, items, qbeg, in, out, ws);
   return hipGetLastError();
 }
 

@@ -26,14 +26,9 @@ const char* mfma_kernel_name(const PassDesc& p);
 
 // One phase of the batched persistent launch (tile_lg 11..13: tiles of
 // 2^tile_lg elements, 2^tile_lg / 16 threads per workgroup).  qbeg[0..8]
-// bounds the eight queues of the phase in `items`; the heads
-// heads[kHeadStride * q], q < 8, must be zero (launch_batch_clear) before the
-// launch.
-constexpr int kHeadStride = 32;
+// bounds the eight queues of the phase in `items`; grid >= 8.
 hipError_t launch_batch(int tile_lg, const BatchPass* passes, const int2* items, const int* qbeg,
-                        int* heads, const float2* in, float2* out, float2* ws, int grid,
-                        hipStream_t s);
-hipError_t launch_batch_clear(int* heads, int n, hipStream_t s);
+                        const float2* in, float2* out, float2* ws, int grid, hipStream_t s);
 size_t batch_lds_bytes(int tile);
 int batch_occupancy(int tile_lg);        // resident workgroups per CU (0 on error)
 const char* batch_kernel_name(int tile_lg);
