@@ -1573,7 +1573,8 @@ WavePlan* build_wave_plan(int d, const i64* Mrm, const i64* Jrm, int levels, i64
 
 namespace {
 // Batched channel plans: one lattice per (small level, signal, wavelet
-// channel) and one per signal for the final low-pass channel.  dec: staging
+// channel) and one per signal for the final low-pass channel, where the
+// fixed-tile schedule covers them.  dec: staging
 // -> coefficients (inverse FFTs), rec: coefficients -> staging (forward
 // FFTs).
 void build_channel_batches(WavePlan* w) {
@@ -1603,10 +1604,21 @@ void build_channel_batches(WavePlan* w) {
       }
     }
   };
-  for (int l = w->small_from; l < w->levels; ++l)
-    add(w->lv[l].Nl, w->lv[l].ml / q, q - 1, w->stage_lvl[l], coeff_off[l]);
-  add(w->lv[w->levels - 1].Nl, w->lv[w->levels - 1].ml / q, 1, w->stage_d1, coeff_off[w->levels]);
+  w->chan_batched.assign(w->levels, 0);
+  for (int l = w->small_from; l < w->levels; ++l) {
+    const WaveLevel& V = w->lv[l];
+    // (a long chirp-z axis needs more workspace than the staging leaves it)
+    if (V.fftN->chirp_ws) throw StatusError{E_UNSUPPORTED};
+    bool fits = V.ml / q >= 32 && V.ml / q <= (i64(1) << 26);
+    for (i64 e : V.fftN->eps) fits = fits && is_pow2(e);
+    w->chan_batched[l] = fits;
+    if (fits) add(V.Nl, V.ml / q, q - 1, w->stage_lvl[l], coeff_off[l]);
+  }
+  const WaveLevel& E = w->lv[w->levels - 1];
+  w->d1_batched = w->chan_batched[w->levels - 1] != 0;
+  if (w->d1_batched) add(E.Nl, E.ml / q, 1, w->stage_d1, coeff_off[w->levels]);
   const int count = (int)st.size();
+  if (count == 0) return;
   // tiles of 2^13 elements; the forward channels (reconstruction) take
   // their smallest radix first (the fastest of the measured schedules on
   // 2^16 .. 2^22 point channels)

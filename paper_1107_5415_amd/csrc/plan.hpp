@@ -169,13 +169,17 @@ struct WavePlan {
   bool uploaded = false;    // every device table of the pyramid is resident
   size_t ws_elems = 0;
   // Channel FFTs of the small levels (small_from .. levels-1, and the final
-  // low-pass channel) run as one batched launch: the splits leave their
-  // Fourier channels in a staging area of the workspace, one inverse batched
-  // launch writes them to the coefficients (and a forward one reads them back
-  // for the reconstruction).  small_from == levels: no batching.
+  // low-pass channel): the splits leave their Fourier channels in a staging
+  // area of the workspace, from where inverse FFTs write the coefficients (and
+  // forward ones read them back for the reconstruction).  Channels the
+  // fixed-tile schedule covers (chan_batched per level, d1_batched) run as one
+  // batched launch pair, the others level by level.  small_from == levels: no
+  // staging.
   int small_from = 0;
   BatchPlan* chan_dec = nullptr;
   BatchPlan* chan_rec = nullptr;
+  std::vector<char> chan_batched;
+  bool d1_batched = false;
   std::vector<i64> stage_lvl;   // staging offset of level l's d2hat ([B][m_l/2])
   i64 stage_d1 = 0;             // staging offset of the final d1hat
   size_t fw_elems = 0;          // FFT workspace region (main stream)

@@ -103,6 +103,44 @@ long long coeff_offset(const WavePlan* w, int level) {
   return off;
 }
 
+// Channel FFTs of the small levels and of the final low-pass channel between
+// the staging area ([B][q-1][m_l/q] per level, then [B][m_L/q]) and the
+// coefficients; dec: inverse FFTs to the coefficients, else forward ones from
+// them.  One launch pair over every channel the fixed-tile schedule covers;
+// the others level by level, over the signals or over the channels of one,
+// whichever takes fewer launches (a launch per signal and channel took most of
+// the time of pyramids whose lattices are no powers of two).
+template <class P>
+void staged_channels(const WavePlan* w, bool dec, float2* st, P* coeffs, float2* fw,
+                     hipStream_t s) {
+  const long long B = w->batch, m = w->m, q = w->q;
+  float2* c = const_cast<float2*>(coeffs);   // written when dec
+  if (dec && w->chan_dec) exec_batch(w->chan_dec, true, BATCH_PERSISTENT, st, c, fw, s);
+  if (!dec && w->chan_rec) exec_batch(w->chan_rec, false, BATCH_PERSISTENT, c, st, fw, s);
+  auto run = [&](const LatticePlan* p, long long so, long long sb, long long co, long long cb) {
+    if (dec)
+      exec_lattice(p, true, false, false, st + so, c + co, fw, sb, cb, s);
+    else
+      exec_lattice(p, false, false, false, c + co, st + so, fw, cb, sb, s);
+  };
+  long long off = 0;
+  for (int l = 0; l < w->levels; ++l) {
+    const WaveLevel& V = w->lv[l];
+    const long long n = V.ml / q;
+    if (l >= w->small_from && !w->chan_batched[l]) {
+      if (q - 1 <= B)
+        for (long long j = 0; j < q - 1; ++j)
+          run(V.fftN, w->stage_lvl[l] + j * n, (q - 1) * n, off + j * n, m);
+      else
+        for (long long i = 0; i < B; ++i)
+          run(V.fftW, w->stage_lvl[l] + i * (q - 1) * n, n, i * m + off, n);
+    }
+    off += (q - 1) * n;
+  }
+  const WaveLevel& E = w->lv[w->levels - 1];
+  if (!w->d1_batched) run(E.fftN, w->stage_d1, E.ml / q, off, m);
+}
+
 // Levels fused into one split/unsplit launch (at most kMaxChain).
 constexpr int kChainLevels = 2;
 
@@ -110,7 +148,7 @@ constexpr int kChainLevels = 2;
 // the batched staging area for small levels, the second stream's buffer for
 // large ones, D2 otherwise.
 float2* d2_slot(const WavePlan* w, const Bufs& b, int l) {
-  const bool batched = w->chan_dec != nullptr;
+  const bool batched = w->small_from < w->levels;
   if (batched && l >= w->small_from) return b.ST + w->stage_lvl[l];
   if (l < w->small_from) return b.BD + w->big_d2[l];
   return b.D2;
@@ -169,7 +207,7 @@ void decompose_runs(const WavePlan* w, const float2* x, const float* const* mask
   Bufs b = carve(w, ws);
   const long long B = w->batch, m = w->m;
   const int L = w->levels;
-  const bool batched = w->chan_dec != nullptr;
+  const bool batched = w->small_from < w->levels;
   float2* cur = b.F0;
   top_forward(w, x, cur, b.FW, m, w->lv[0].ml, s, -1);
   bool forked = false;
@@ -198,7 +236,7 @@ void decompose_runs(const WavePlan* w, const float2* x, const float* const* mask
     cur = next;
   }
   if (batched) {
-    exec_batch(w->chan_dec, true, BATCH_PERSISTENT, b.ST, coeffs, b.FW, s);
+    staged_channels(w, true, b.ST, coeffs, b.FW, s);
   } else {
     const WaveLevel& VL = w->lv[L - 1];
     exec_lattice(VL.fftN, true, false, false, cur, coeffs + coeff_offset(w, L), b.FW, VL.ml / 2, m,
@@ -213,7 +251,7 @@ void reconstruct_runs(const WavePlan* w, const float2* coeffs, const float* cons
   Bufs b = carve(w, ws);
   const long long B = w->batch, m = w->m;
   const int L = w->levels;
-  const bool batched = w->chan_rec != nullptr;
+  const bool batched = w->small_from < w->levels;
   const auto runs = level_runs(w, b);
   const int nr = (int)runs.size();
   // run i (0 = finest) writes F0 or F1 alternately upwards from the finest
@@ -233,7 +271,7 @@ void reconstruct_runs(const WavePlan* w, const float2* coeffs, const float* cons
     }
   }
   if (batched)
-    exec_batch(w->chan_rec, false, BATCH_PERSISTENT, coeffs, b.ST, b.FW, s);
+    staged_channels(w, false, b.ST, coeffs, b.FW, s);
   else
     exec_lattice(VL.fftN, false, false, false, coeffs + coeff_offset(w, L), cur, b.FW, m,
                  VL.ml / 2, s);
@@ -327,7 +365,7 @@ void decompose_q(const WavePlan* w, const float2* x, const float* const* masks, 
   QBufs b = carve_q(w, ws);
   const long long B = w->batch, m = w->m, q = w->q;
   const int L = w->levels;
-  const bool batched = w->chan_dec != nullptr;
+  const bool batched = w->small_from < w->levels;
   const std::vector<long long> soff = saved_offsets(w);
   float2* cur = keep ? keep : b.F0;
   top_forward(w, x, cur, b.FW, m, m, s, basis);
@@ -355,7 +393,7 @@ void decompose_q(const WavePlan* w, const float2* x, const float* const* masks, 
     cur = next;
   }
   if (batched) {
-    exec_batch(w->chan_dec, true, BATCH_PERSISTENT, b.ST, coeffs, b.FW, s);
+    staged_channels(w, true, b.ST, coeffs, b.FW, s);
   } else {
     const WaveLevel& VL = w->lv[L - 1];
     exec_lattice(VL.fftN, true, false, false, cur, coeffs + coeff_offset_q(w, L), b.FW, VL.ml / q,
@@ -374,11 +412,11 @@ void reconstruct_q(const WavePlan* w, const float2* coeffs, const float* const* 
   const std::vector<long long> soff = saved_offsets(w);
   const long long B = w->batch, m = w->m, q = w->q;
   const int L = w->levels;
-  const bool batched = w->chan_rec != nullptr;
+  const bool batched = w->small_from < w->levels;
   const WaveLevel& VL = w->lv[L - 1];
   float2* cur;
   if (batched) {
-    exec_batch(w->chan_rec, false, BATCH_PERSISTENT, coeffs, b.ST, b.FW, s);
+    staged_channels(w, false, b.ST, coeffs, b.FW, s);
     cur = b.ST + w->stage_d1;
   } else {
     cur = q_target(b, L);
@@ -453,7 +491,7 @@ void wave_decompose(const WavePlan* w, const float2* x, const float* const* mask
   Bufs b = carve(w, ws);
   const long long B = w->batch, m = w->m;
   const int L = w->levels;
-  const bool batched = w->chan_dec != nullptr;
+  const bool batched = w->small_from < w->levels;
   float2* cur = saved;
   top_forward(w, x, cur, b.FW, m, w->lv[0].ml, s, -1);
   long long soff = 0;
@@ -481,7 +519,7 @@ void wave_decompose(const WavePlan* w, const float2* x, const float* const* mask
   }
   if (batched) {
     // every small channel and the final low-pass channel in one launch pair
-    exec_batch(w->chan_dec, true, BATCH_PERSISTENT, b.ST, coeffs, b.FW, s);
+    staged_channels(w, true, b.ST, coeffs, b.FW, s);
   } else {
     const WaveLevel& VL = w->lv[L - 1];
     exec_lattice(VL.fftN, true, false, false, cur, coeffs + coeff_offset(w, L), b.FW, VL.ml / 2, m,
