@@ -3,13 +3,20 @@
 // tiles).
 //
 // Every workgroup stays resident and walks a contiguous range of tiles of
-// its XCD; two workgroups per CU overlap one tile's HBM traffic with the
-// other's arithmetic.  A tile is transformed by radix-32/16/8 Stockham
-// stages in VGPRs with padded LDS transposes between stages.  Pencil length
-// L, pencils per tile W and the radix sequence are compile-time constants,
-// so the butterfly geometry and the LDS offsets fold to constants; the
-// tile's signal and pencil indices are uniform (scalar unit) and every
-// global access is a 32-bit offset from a uniform base.
+// its XCD, 16 waves per CU (two workgroups of 8192-element tiles, one of
+// 16384), so that one wave's HBM traffic overlaps another's arithmetic.  A
+// tile is transformed by radix-16/8 Stockham stages in VGPRs with padded LDS
+// transposes between stages.  Pencil length L, pencils per tile W and the
+// radix sequence are compile-time constants, so the butterfly geometry and the
+// LDS offsets fold to constants; the tile's signal and pencil indices are
+// uniform (scalar unit) and every global access is a 32-bit offset from a
+// uniform base.
+//
+// 16 values per thread: 32 need 185 .. 256 VGPRs and leave 8 waves per CU,
+// with one exchange less (8192 = 32 16 16 against 16 8 8 8).  2^24 points
+// forward and back took 314 us with 32 values, 294 with 16; the same with
+// real and imaginary parts exchanged separately in the 16384-element tiles
+// (half the LDS, twice the barriers): 293, but the pyramids 1% slower.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -22,27 +29,22 @@ namespace lfft {
 namespace {
 using namespace dev;
 
-constexpr int kP = 32;  // values per thread
-// workgroups per CU the register budget is sized for
-constexpr int kRowsWgPerCu = 2;
-constexpr int kColsWgPerCu = 1;
-// exchange real and imaginary parts separately for row tiles (halves LDS)
-constexpr bool kSplitRows = false;
+constexpr int kP = 16;         // values per thread
+constexpr int kWavesPerSimd = 4;   // the register budget (128 VGPRs)
 
 __device__ __forceinline__ int sphys(int e) { return e + (e >> 4); }
 
-// Radix sequence of a pencil of length L with 32 values per thread: a
-// radix-32 first stage (no twiddles) and radix-16/8 stages after it.
+// Radix sequence of a pencil of length L with 16 values per thread.
 __host__ __device__ constexpr int seq_radix(int L, int s) {
-  return L == 8192 ? (s == 0 ? 32 : 16)
-       : L == 4096 ? (s == 0 ? 32 : s == 1 ? 16 : 8)
-       : L == 2048 ? (s == 0 ? 32 : 8)
-       : L == 1024 ? 32
-       : L == 512 ? (s == 0 ? 32 : 16)
+  return L == 8192 ? (s == 0 ? 16 : 8)
+       : L == 4096 ? 16
+       : L == 2048 ? (s < 2 ? 16 : 8)
+       : L == 1024 ? (s == 0 ? 16 : 8)
+       : L == 512 ? 8
        : 16;  // 256
 }
 __host__ __device__ constexpr int seq_len(int L) {
-  return (L == 8192 || L == 4096 || L == 2048) ? 3 : 2;
+  return L == 8192 ? 4 : L >= 512 ? 3 : 2;
 }
 __host__ __device__ constexpr int seq_ns(int L, int s) {
   return s == 0 ? 1 : seq_ns(L, s - 1) * seq_radix(L, s - 1);
@@ -61,7 +63,7 @@ struct StageNs {
 };
 template <int R>
 struct Lg {
-  static constexpr int value = R == 32 ? 5 : R == 16 ? 4 : R == 8 ? 3 : R == 4 ? 2 : 1;
+  static constexpr int value = R == 16 ? 4 : R == 8 ? 3 : R == 4 ? 2 : 1;
 };
 
 // One side (input or output) of a tile: the signal's base pointer is uniform
@@ -271,9 +273,9 @@ __device__ __forceinline__ int slds_off(int base_e, int delta) {
   return base_e + d + (d >> 4);
 }
 
-// write stage SI outputs, read stage SI+1 inputs (one part: 0 both, 1 re, 2 im)
-template <int L, int W, bool COLS, int SI, int PART>
-__device__ __forceinline__ void exch_write(const float2* v, void* lds, int jt, int w) {
+// write stage SI outputs, read stage SI+1 inputs
+template <int L, int W, bool COLS, int SI>
+__device__ __forceinline__ void exch_write(const float2* v, float2* lds, int jt, int w) {
   constexpr int R = StageR<L, SI>::value;
   constexpr int Ns = StageNs<L, SI>::value;
   constexpr int TPP = L / kP;
@@ -288,18 +290,13 @@ __device__ __forceinline__ void exch_write(const float2* v, void* lds, int jt, i
 #pragma unroll
     for (int i = 0; i < R; ++i) {
       const int e = lin ? slds_off<COLS, L, W>(eb, i * Ns) : slds<COLS, L, W>(out0 + i * Ns, w);
-      if constexpr (PART == 0)
-        static_cast<float2*>(lds)[e] = v[q * R + i];
-      else if constexpr (PART == 1)
-        static_cast<float*>(lds)[e] = v[q * R + i].x;
-      else
-        static_cast<float*>(lds)[e] = v[q * R + i].y;
+      lds[e] = v[q * R + i];
     }
   }
 }
 
-template <int L, int W, bool COLS, int SI, int PART>
-__device__ __forceinline__ void exch_read(float2* v, const void* lds, int jt, int w, int off) {
+template <int L, int W, bool COLS, int SI>
+__device__ __forceinline__ void exch_read(float2* v, const float2* lds, int jt, int w, int off) {
   constexpr int R = StageR<L, SI>::value;
   constexpr int TPP = L / kP;
   static_assert((L / R) % 16 == 0, "read stride must keep LDS offsets linear");
@@ -310,43 +307,27 @@ __device__ __forceinline__ void exch_read(float2* v, const void* lds, int jt, in
 #pragma unroll
     for (int i = 0; i < R; ++i) {
       const int e = slds_off<COLS, L, W>(eb, i * (L / R));
-      if constexpr (PART == 0)
-        v[q * R + i] = static_cast<const float2*>(lds)[e];
-      else if constexpr (PART == 1)
-        v[q * R + i].x = static_cast<const float*>(lds)[e];
-      else
-        v[q * R + i].y = static_cast<const float*>(lds)[e];
+      v[q * R + i] = lds[e];
     }
   }
 }
 
-template <int L, int W, bool COLS, bool SPLIT, int SI>
-__device__ __forceinline__ void stages_from(float2* v, float2* twb, void* lds, const PassDesc& p,
+template <int L, int W, bool COLS, int SI>
+__device__ __forceinline__ void stages_from(float2* v, float2* twb, float2* lds, const PassDesc& p,
                                             int jt, int w, int off) {
   constexpr int NS = NStages<L>::value;
   stage_compute<L, SI>(v, twb, p.sign);
   if constexpr (SI + 1 < NS) {
     tw_load<L, SI + 1>(twb, p, jt, off);
-    if constexpr (!SPLIT) {
-      exch_write<L, W, COLS, SI, 0>(v, lds, jt, w);
-      __syncthreads();
-      exch_read<L, W, COLS, SI + 1, 0>(v, lds, jt, w, off);
-      __syncthreads();
-    } else {
-      exch_write<L, W, COLS, SI, 1>(v, lds, jt, w);
-      __syncthreads();
-      exch_read<L, W, COLS, SI + 1, 1>(v, lds, jt, w, off);
-      __syncthreads();
-      exch_write<L, W, COLS, SI, 2>(v, lds, jt, w);
-      __syncthreads();
-      exch_read<L, W, COLS, SI + 1, 2>(v, lds, jt, w, off);
-      __syncthreads();
-    }
-    stages_from<L, W, COLS, SPLIT, SI + 1>(v, twb, lds, p, jt, w, off);
+    exch_write<L, W, COLS, SI>(v, lds, jt, w);
+    __syncthreads();
+    exch_read<L, W, COLS, SI + 1>(v, lds, jt, w, off);
+    __syncthreads();
+    stages_from<L, W, COLS, SI + 1>(v, twb, lds, p, jt, w, off);
   }
 }
 
-template <int L, bool COLS, int MOUT>
+template <int L, bool COLS, bool POST, int MOUT>
 __device__ __forceinline__ void store_tile(const float2* v, const PassDesc& p,
                                            float2* __restrict__ out, const TileId& t, int w,
                                            int jt, int off) {
@@ -360,14 +341,14 @@ __device__ __forceinline__ void store_tile(const float2* v, const PassDesc& p,
   side_init<MOUT>(A, p.out, out, t.b, o, s, L, p.S);
   float2* base = const_cast<float2*>(A.base);
   const bool scaled = p.scale != 1.0f;
-  const unsigned lo = p.post ? post_lo(p, s) : 0u;
+  const unsigned lo = POST ? post_lo(p, s) : 0u;
 #pragma unroll
   for (int q = 0; q < kP / R; ++q) {
     const int out0 = turned<L, NS - 1>(jt + TPP * q, off);
     side_positions<MOUT, R>(A, p.out, p.S, out0, Ns, [&](int i, int off) {
       float2 x = v[q * R + i];
       // (the pencil is one digit, the four-step axis's high one)
-      if (p.post) x = c_mul(x, post_twiddle(p, (unsigned)(out0 + i * Ns) * lo));
+      if constexpr (POST) x = c_mul(x, post_twiddle(p, (unsigned)(out0 + i * Ns) * lo));
       if (scaled) {
         x.x *= p.scale;
         x.y *= p.scale;
@@ -388,11 +369,11 @@ __device__ __forceinline__ void store_tile(const float2* v, const PassDesc& p,
 // Every launch satisfies (checked on the host): W divides the pencils of one
 // signal (O * S), so all tiles are full and never straddle two signals, and
 // one signal has fewer than 2^28 points (32-bit element offsets).
-template <int L, int W, bool COLS, bool SPLIT, int MIN, int MOUT>
-__global__ void __launch_bounds__(W * L / kP, (COLS ? kColsWgPerCu : kRowsWgPerCu)) fft_stream_kernel(PassDesc p, const float2* __restrict__ in,
-                                                                float2* __restrict__ out) {
-  extern __shared__ float2 lds_raw[];
-  void* lds = lds_raw;
+// POST: the four-step twiddle follows (column tiles onto the grid only).
+template <int L, int W, bool COLS, bool POST, int MIN, int MOUT>
+__global__ void __launch_bounds__(W* L / kP, kWavesPerSimd)
+    fft_stream_kernel(PassDesc p, const float2* __restrict__ in, float2* __restrict__ out) {
+  extern __shared__ float2 lds[];
   constexpr int TPP = L / kP;
   const int tid = threadIdx.x;
   int w = COLS ? tid % W : tid / TPP;
@@ -425,8 +406,8 @@ __global__ void __launch_bounds__(W * L / kP, (COLS ? kColsWgPerCu : kRowsWgPerC
   for (; tile < end; tile += nwg_x) {
     const TileId ta = tile_of<W>(tile, p.O, p.S);
     load_tile<L, COLS, MIN>(va, p, in, ta, w, jt);
-    stages_from<L, W, COLS, SPLIT, 0>(va, twb, lds, p, jt, w, off);
-    store_tile<L, COLS, MOUT>(va, p, out, ta, w, jt, off);
+    stages_from<L, W, COLS, 0>(va, twb, lds, p, jt, w, off);
+    store_tile<L, COLS, POST, MOUT>(va, p, out, ta, w, jt, off);
   }
 }
 
@@ -434,12 +415,12 @@ __global__ void __launch_bounds__(W * L / kP, (COLS ? kColsWgPerCu : kRowsWgPerC
 // first use; threads that race here all store the same values
 std::atomic<int> g_cus{0};
 
-template <int L, int W, bool COLS, bool SPLIT, int MIN, int MOUT>
+template <int L, int W, bool COLS, bool POST, int MIN, int MOUT>
 hipError_t launch_t(const PassDesc& p, const float2* in, float2* out, hipStream_t s) {
-  auto kern = fft_stream_kernel<L, W, COLS, SPLIT, MIN, MOUT>;
+  auto kern = fft_stream_kernel<L, W, COLS, POST, MIN, MOUT>;
   constexpr int NT = W * L / kP;
   constexpr int tile = W * L;
-  constexpr size_t lds = (size_t)(tile + tile / 16 + 1) * (SPLIT ? sizeof(float) : sizeof(float2));
+  constexpr size_t lds = (size_t)(tile + tile / 16 + 1) * sizeof(float2);
   static std::atomic<int> wgs_cache{0};
   int wgs_per_cu = wgs_cache.load(std::memory_order_acquire);
   if (!wgs_per_cu) {
@@ -469,31 +450,17 @@ hipError_t launch_t(const PassDesc& p, const float2* in, float2* out, hipStream_
   return hipGetLastError();
 }
 
-// Exchange real and imaginary parts separately when the tile would not fit
-// 72 KB of LDS as complex values, except for the 2048 x 8 column tiles with a
-// natural side: one workgroup per CU holds their 139 KB complex tile, and
-// whole complex exchanges (half the barriers) measured 2% faster on the step
-// without spilling registers.
-__host__ __device__ constexpr bool stream_split(int L, int W, bool cols, int min, int mout) {
-  return (cols && L == 2048 && W == 8 && mout != MAP_LINEAR &&
-          (min == MAP_NATURAL || mout == MAP_NATURAL))
-             ? false
-             : ((cols || kSplitRows) ? ((long long)W * L * 17 / 16 * 8 > 72 * 1024 || kSplitRows)
-                                     : false);
-}
-
 template <int L, int W, bool COLS, int MIN>
 hipError_t launch_o(const PassDesc& p, const float2* in, float2* out, hipStream_t s) {
   switch (p.out.mode) {
     case MAP_IDENTITY:
-      return launch_t<L, W, COLS, stream_split(L, W, COLS, MIN, MAP_IDENTITY), MIN, MAP_IDENTITY>(
-          p, in, out, s);
+      if constexpr (COLS)
+        if (p.post) return launch_t<L, W, true, true, MIN, MAP_IDENTITY>(p, in, out, s);
+      return launch_t<L, W, COLS, false, MIN, MAP_IDENTITY>(p, in, out, s);
     case MAP_LINEAR:
-      return launch_t<L, W, COLS, stream_split(L, W, COLS, MIN, MAP_LINEAR), MIN, MAP_LINEAR>(
-          p, in, out, s);
+      return launch_t<L, W, COLS, false, MIN, MAP_LINEAR>(p, in, out, s);
     default:
-      return launch_t<L, W, COLS, stream_split(L, W, COLS, MIN, MAP_NATURAL), MIN, MAP_NATURAL>(
-          p, in, out, s);
+      return launch_t<L, W, COLS, false, MIN, MAP_NATURAL>(p, in, out, s);
   }
 }
 
@@ -522,13 +489,14 @@ const char* stream_kernel_name(const PassDesc& p) {
   const int W = p.W;
   const int min = p.in.mode == MAP_NATURAL ? 2 : 0;
   const int mout = p.out.mode;
-  const bool split = stream_split(p.L, W, cols, min, mout);
   return kernel_name_intern("fft_stream_kernel<%d, %d, %s, %s, %d, %d>", p.L, W,
-                            cols ? "true" : "false", split ? "true" : "false", min, mout);
+                            cols ? "true" : "false", p.post ? "true" : "false", min, mout);
 }
 
 hipError_t launch_stream_pass(const PassDesc& p, const float2* in, float2* out, hipStream_t s) {
   const bool cols = p.S > 1;
+  // a four-step pass has the low digit behind it and ends on the grid
+  if (p.post && (!cols || p.out.mode != MAP_IDENTITY)) return hipErrorInvalidValue;
   if (!cols) {
     switch (p.L) {
       case 8192: return launch_i<8192, 1, false>(p, in, out, s);
