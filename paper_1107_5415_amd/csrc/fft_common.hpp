@@ -242,6 +242,20 @@ __device__ __forceinline__ long long xcd_tile(long long i, long long n) {
   return x * per + (x < rem ? x : rem) + k;
 }
 
+// Touch every 64-byte line of the kernel's first BYTES bytes of arguments at
+// once.  The pass descriptor spans two dozen lines outside the device's own
+// memory; read where they are needed, one dependent step after the other, each
+// new line adds its latency to every wave.
+template <int BYTES>
+__device__ __forceinline__ void touch_args() {
+  typedef const __attribute__((address_space(4))) int* Arg;
+  const Arg k = (Arg)__builtin_amdgcn_kernarg_segment_ptr();
+  int acc = 0;
+#pragma unroll
+  for (int i = 0; i < (BYTES + 63) / 64; ++i) acc |= k[16 * i];
+  asm volatile("" ::"s"(acc));
+}
+
 // Non-temporal 8-byte load and store: the line is not kept for reuse.  For
 // data read or written once by a call (whole lines, so that no other wave
 // has to fetch the same line again), which leaves the caches to the data

@@ -112,10 +112,11 @@ FastDiv make_fast_div(i64 d) {
 
 // Radices of the mixed-radix kernel for a digit of length n: the fewest
 // stages of radix 2 .. 16 or a prime (an LDS round trip and a barrier each),
-// then the smallest sum.  Primes above 16 go between the others where they
-// can: the first and the last stage of a pass load and store through the maps
-// without a pass over LDS only up to radix 16.
-std::vector<int> radices_of(i64 n) {
+// then the smallest sum.  The first and the last stage of a pass load and
+// store through the maps without a pass over LDS only up to radix 16, so a
+// prime above 16 stands at neither end where it can, and rather first (no
+// twiddles) than last.  first, last: the digit opens or closes the pencil.
+std::vector<int> radices_of(i64 n, bool first, bool last) {
   std::vector<i64> divs, cand;
   for (i64 c = 1; c <= n; ++c)
     if (n % c == 0) divs.push_back(c);
@@ -144,9 +145,10 @@ std::vector<int> radices_of(i64 n) {
     c /= r;
   }
   std::sort(small.rbegin(), small.rend());
-  if (!small.empty()) out.push_back(small.front());
+  const size_t lead = first && small.size() > (last ? 1 : 0) ? 1 : 0;
+  out.assign(small.begin(), small.begin() + (long)lead);
   out.insert(out.end(), large.begin(), large.end());
-  if (small.size() > 1) out.insert(out.end(), small.begin() + 1, small.end());
+  out.insert(out.end(), small.begin() + (long)lead, small.end());
   return out;
 }
 
@@ -703,7 +705,9 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
     for (int g = R.a; g < R.b && pd.kind < 4; ++g) {
       int stride = (int)range_count(dg, g + 1, R.b);
       i64 Ns = 1;
-      std::vector<int> rads = pd.kind == 1 ? pow2_radices(dg[g].n) : radices_of(dg[g].n);
+      // (kinds 1 to 3 take power-of-two digits only, largest radix first)
+      std::vector<int> rads = pd.kind == 0 ? radices_of(dg[g].n, g == R.a, g == R.b - 1)
+                                           : pow2_radices(dg[g].n);
       if (pd.kind == 1 && (p->order & 2)) std::reverse(rads.begin(), rads.end());
       for (int r : rads) {
         if (pd.nst >= kMaxStages) throw StatusError{E_UNSUPPORTED};
