@@ -40,14 +40,18 @@ hipError_t launch_split(const SplitDesc& sd, long long batch, const float2* ahat
 hipError_t launch_unsplit(const SplitDesc& sd, long long batch, const float2* d1, const float2* d2,
                           long long d_bs, const float* mask, float2* ahat, long long ah_bs,
                           hipStream_t s);
-// d loss / d mask of the split, summed over the batch.
-hipError_t launch_split_mask_grad(const SplitDesc& sd, long long batch, const float2* ahat,
-                                  long long ah_bs, const float2* g1, const float2* g2,
-                                  long long g_bs, float* gmask, hipStream_t s);
-// d loss / d mask of the unsplit, summed over the batch.
-hipError_t launch_unsplit_mask_grad(const SplitDesc& sd, long long batch, const float2* d1,
-                                    const float2* d2, long long d_bs, const float2* g,
-                                    long long g_bs, float* gmask, hipStream_t s);
+// Adjoint of the split (g1, g2 -> ga) with d loss / d mask, summed over the
+// batch, from the split's input ahat.
+hipError_t launch_unsplit_grad(const SplitDesc& sd, long long batch, const float2* ahat,
+                               long long ah_bs, const float2* g1, const float2* g2, long long g_bs,
+                               const float* mask, float2* ga, long long ga_bs, float* gmask,
+                               hipStream_t s);
+// Adjoint of the unsplit (g -> e1, e2) with d loss / d mask, summed over the
+// batch, from the unsplit's inputs d1, d2.
+hipError_t launch_split_grad(const SplitDesc& sd, long long batch, const float2* d1,
+                             const float2* d2, long long d_bs, const float2* g, long long g_bs,
+                             const float* mask, float2* e1, float2* e2, long long e_bs,
+                             float* gmask, hipStream_t s);
 
 // Levels l .. l+K-1 (2 <= K <= kMaxChain, every level narrow) of the q = 2
 // split in one launch: ahat [B][m_l] -> d2 of every level (c.d2) and the

@@ -602,11 +602,13 @@ void wave_decompose_backward(const WavePlan* w, const float2* gc, const float2* 
     const WaveLevel& V = w->lv[l];
     const long long half = V.ml / 2;
     exec_lattice(V.fftN, false, false, false, gc + coeff_offset(w, l), b.D2, b.FW, m, half, s);
-    if (gmasks && gmasks[l] && saved)
-      check(launch_split_mask_grad(V.sd, B, saved + soff[l], V.ml, g1, b.D2, half, gmasks[l], s));
     float2* next = (l == 0) ? b.F0 : ((g1 == b.F0) ? b.F1 : b.F0);
     // adjoint of the split is the unsplit with the same masks
-    check(launch_unsplit(V.sd, B, g1, b.D2, half, masks[l], next, V.ml, s));
+    if (gmasks && gmasks[l] && saved)
+      check(launch_unsplit_grad(V.sd, B, saved + soff[l], V.ml, g1, b.D2, half, masks[l], next,
+                                V.ml, gmasks[l], s));
+    else
+      check(launch_unsplit(V.sd, B, g1, b.D2, half, masks[l], next, V.ml, s));
     g1 = next;
   }
   // adjoint of the top-level forward transform (with LWT_SAMPLES its real
@@ -638,12 +640,13 @@ void wave_reconstruct_backward(const WavePlan* w, const float2* gx, const float2
   for (int l = 0; l < L; ++l) {
     const WaveLevel& V = w->lv[l];
     const long long half = V.ml / 2;
-    if (gmasks && gmasks[l] && saved)
-      check(launch_unsplit_mask_grad(V.sd, B, saved + soff[l], saved + soff[l] + B * half, half, g,
-                                     V.ml, gmasks[l], s));
     float2* next = (g == b.F0) ? b.F1 : b.F0;
     // adjoint of the unsplit is the split with the same masks
-    check(launch_split(V.sd, B, g, V.ml, masks[l], next, b.D2, half, s));
+    if (gmasks && gmasks[l] && saved)
+      check(launch_split_grad(V.sd, B, saved + soff[l], saved + soff[l] + B * half, half, g, V.ml,
+                              masks[l], next, b.D2, half, gmasks[l], s));
+    else
+      check(launch_split(V.sd, B, g, V.ml, masks[l], next, b.D2, half, s));
     exec_lattice(V.fftN, true, false, false, b.D2, gc + coeff_offset(w, l), b.FW, half, m, s);
     g = next;
   }

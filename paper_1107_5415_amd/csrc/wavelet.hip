@@ -91,15 +91,26 @@ __global__ void unsplit_kernel(SplitDesc sd, long long batch, const float2* __re
 // Re(conj(g) * x)
 __device__ __forceinline__ float re_dot(float2 g, float2 x) { return g.x * x.x + g.y * x.y; }
 
-__global__ void split_mask_grad_kernel(SplitDesc sd, long long batch, const float2* __restrict__ ah,
-                                       long long ah_bs, const float2* __restrict__ g1,
-                                       const float2* __restrict__ g2, long long g_bs,
-                                       float* __restrict__ gmask) {
+// The adjoints with mask gradients do both in one pass over the incoming
+// gradients, which the two need alike: 24 bytes a point instead of 32.  Bound
+// by HBM; 16 signals, levels of 2^20 .. 2^17 points: split's adjoint and mask
+// gradient 26.6 + 25.4 us a level as two kernels (three levels of the four are
+// 35.6 us as one; the unsplit's 27.7 + 30.8, 37.9 us.
+//
+// Adjoint of the split (the unsplit of g1, g2 into ga) and the gradient of its
+// mask, from its input ah.
+__global__ void unsplit_grad_kernel(SplitDesc sd, long long batch, const float2* __restrict__ ah,
+                                    long long ah_bs, const float2* __restrict__ g1,
+                                    const float2* __restrict__ g2, long long g_bs,
+                                    const float* __restrict__ mask, float2* __restrict__ ga,
+                                    long long ga_bs, float* __restrict__ gmask) {
   long long k = lfft::dev::xcd_tile(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
   if (k >= sd.mN) return;
   Fiber f = fiber_at(sd, k);
   const float2 c = cconj(f.phi);
+  const float a0 = mask[f.i0] * kInvSqrt2, a1 = mask[f.i1] * kInvSqrt2;
   float s0 = 0.f, s1 = 0.f;
+#pragma unroll 2
   for (long long b = 0; b < batch; ++b) {
     float2 x0 = ah[b * ah_bs + f.i0];
     float2 x1 = ah[b * ah_bs + f.i1];
@@ -108,19 +119,29 @@ __global__ void split_mask_grad_kernel(SplitDesc sd, long long batch, const floa
     // d1 = (a0 x0 + a1 x1)/sqrt2, d2 = c (a1 x0 - a0 x1)/sqrt2
     s0 += re_dot(G1, x0) - re_dot(G2, cmul(c, x1));
     s1 += re_dot(G1, x1) + re_dot(G2, cmul(c, x0));
+    const float2 y2 = cmul(f.phi, G2);
+    ga[b * ga_bs + f.i0] = axpby(a0, G1, a1, y2);
+    ga[b * ga_bs + f.i1] = axpby(a1, G1, -a0, y2);
   }
   gmask[f.i0] = s0 * kInvSqrt2;
   gmask[f.i1] = s1 * kInvSqrt2;
 }
 
-__global__ void unsplit_mask_grad_kernel(SplitDesc sd, long long batch, const float2* __restrict__ d1,
-                                         const float2* __restrict__ d2, long long d_bs,
-                                         const float2* __restrict__ g, long long g_bs,
-                                         float* __restrict__ gmask) {
+// Adjoint of the unsplit (the split of g into e1, e2) and the gradient of its
+// mask, from its inputs d1, d2.
+__global__ void split_grad_kernel(SplitDesc sd, long long batch, const float2* __restrict__ d1,
+                                  const float2* __restrict__ d2, long long d_bs,
+                                  const float2* __restrict__ g, long long g_bs,
+                                  const float* __restrict__ mask, float2* __restrict__ e1,
+                                  float2* __restrict__ e2, long long e_bs,
+                                  float* __restrict__ gmask) {
   long long k = lfft::dev::xcd_tile(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
   if (k >= sd.mN) return;
   Fiber f = fiber_at(sd, k);
+  const float2 c = cconj(f.phi);
+  const float a0 = mask[f.i0] * kInvSqrt2, a1 = mask[f.i1] * kInvSqrt2;
   float s0 = 0.f, s1 = 0.f;
+#pragma unroll 2
   for (long long b = 0; b < batch; ++b) {
     float2 y1 = d1[b * d_bs + k];
     float2 y2 = cmul(f.phi, d2[b * d_bs + k]);
@@ -129,6 +150,8 @@ __global__ void unsplit_mask_grad_kernel(SplitDesc sd, long long batch, const fl
     // ah0 = (a0 y1 + a1 y2)/sqrt2, ah1 = (a1 y1 - a0 y2)/sqrt2
     s0 += re_dot(G0, y1) - re_dot(G1, y2);
     s1 += re_dot(G0, y2) + re_dot(G1, y1);
+    e1[b * e_bs + k] = axpby(a0, G0, a1, G1);
+    e2[b * e_bs + k] = cmul(c, axpby(a1, G0, -a0, G1));
   }
   gmask[f.i0] = s0 * kInvSqrt2;
   gmask[f.i1] = s1 * kInvSqrt2;
@@ -543,19 +566,21 @@ hipError_t launch_unsplit(const SplitDesc& sd, long long batch, const float2* d1
   return hipGetLastError();
 }
 
-hipError_t launch_split_mask_grad(const SplitDesc& sd, long long batch, const float2* ah,
-                                  long long ah_bs, const float2* g1, const float2* g2,
-                                  long long g_bs, float* gmask, hipStream_t s) {
-  hipLaunchKernelGGL(split_mask_grad_kernel, dim3(blocks_for(sd.mN, 256)), dim3(256), 0, s, sd,
-                     batch, ah, ah_bs, g1, g2, g_bs, gmask);
+hipError_t launch_unsplit_grad(const SplitDesc& sd, long long batch, const float2* ah,
+                               long long ah_bs, const float2* g1, const float2* g2, long long g_bs,
+                               const float* mask, float2* ga, long long ga_bs, float* gmask,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(unsplit_grad_kernel, dim3(blocks_for(sd.mN, 256)), dim3(256), 0, s, sd, batch,
+                     ah, ah_bs, g1, g2, g_bs, mask, ga, ga_bs, gmask);
   return hipGetLastError();
 }
 
-hipError_t launch_unsplit_mask_grad(const SplitDesc& sd, long long batch, const float2* d1,
-                                    const float2* d2, long long d_bs, const float2* g,
-                                    long long g_bs, float* gmask, hipStream_t s) {
-  hipLaunchKernelGGL(unsplit_mask_grad_kernel, dim3(blocks_for(sd.mN, 256)), dim3(256), 0, s, sd,
-                     batch, d1, d2, d_bs, g, g_bs, gmask);
+hipError_t launch_split_grad(const SplitDesc& sd, long long batch, const float2* d1,
+                             const float2* d2, long long d_bs, const float2* g, long long g_bs,
+                             const float* mask, float2* e1, float2* e2, long long e_bs,
+                             float* gmask, hipStream_t s) {
+  hipLaunchKernelGGL(split_grad_kernel, dim3(blocks_for(sd.mN, 256)), dim3(256), 0, s, sd, batch,
+                     d1, d2, d_bs, g, g_bs, mask, e1, e2, e_bs, gmask);
   return hipGetLastError();
 }
 
