@@ -50,7 +50,7 @@ struct MapDesc {
   // elements, the first of which lies at position 0 of the tile's first row;
   // streaming and register-resident kernels, last pass over columns:
   // chain[w] = (column, position) likewise inside every tile of W columns, in
-  // runs (NULL: in order)
+  // runs, and on the input side of a first pass over columns (NULL: in order)
   const int2* chain;
 };
 

@@ -60,6 +60,14 @@ __device__ __forceinline__ BfGeom geom_turned(const StageDesc& st, int bl, int o
   return g;
 }
 
+// First stage of a one-digit pencil, butterfly `bl` turned by `off` positions
+// on its inputs: with p = (bl + off) mod L value i is input (i + k) mod R of
+// butterfly p mod (L / R), k = p / (L / R); its output m carries the factor
+// w^(-k m), w = exp(sign 2 pi i / R), which start_turn takes off.
+__device__ __forceinline__ int start_bf(const StageDesc& st, int bl, int off) {
+  return off < 0 ? bl : (bl + off) & ((st.n >> st.lg_r) - 1);
+}
+
 // One side of a pencil: the signal's base pointer and 32-bit element
 // offsets inside the signal (the planner keeps these lattices below 2^30
 // points).
@@ -142,11 +150,12 @@ __device__ __forceinline__ void dftR(float2* v, int sign) {
 
 template <int P, int R, int MIN>
 __device__ __forceinline__ void load_first(float2* v, const PassDesc& p, const Addr<MIN>& A,
-                                           int jt, int TPP, bool active) {
+                                           int jt, int TPP, bool active, int off) {
   const StageDesc& st = p.st[0];
 #pragma unroll
   for (int q = 0; q < P / R; ++q) {
     BfGeom g = geom(st, jt + TPP * q);
+    if (off >= 0) g.in0 = (jt + TPP * q + off) & (st.n - 1);
     if (active) {
       for_positions<MIN, R>(A, p.in, p.S, g.in0, g.in_step,
                             [&](int i, int off) { v[q * R + i] = A.base[(unsigned)off]; });
@@ -207,6 +216,20 @@ __device__ __forceinline__ void apply_tw(float2* x, const float2* b, int sign) {
   for (int i = 1; i < R; ++i) x[i] = c_mul(x[i], pw[i]);
 }
 
+template <int P, int R>
+__device__ __forceinline__ void start_turn(float2* v, const StageDesc& st, int sign, int jt,
+                                           int TPP, int off) {
+  constexpr int LG = R == 16 ? 4 : R == 8 ? 3 : R == 4 ? 2 : 1;
+#pragma unroll
+  for (int q = 0; q < P / R; ++q) {
+    const int kT = (jt + TPP * q + off) & (st.n - (st.n >> st.lg_r));   // k L / R, k < R
+    float2 b[LG];
+#pragma unroll
+    for (int i = 0; i < LG; ++i) b[i] = st.tw[(kT << i) & (st.n - 1)];
+    apply_tw<R>(&v[q * R], b, sign);
+  }
+}
+
 // tw: the stage has twiddles (Ns > 1; the first stage of a digit has none)
 template <int P, int R>
 __device__ __forceinline__ void compute_stage(float2* v, const float2* twb, int sign, bool tw) {
@@ -244,10 +267,10 @@ __device__ __forceinline__ void for_lds(int l0, int step, int w, int W, int PR, 
 
 template <int P, int R, bool COLS, int PART>
 __device__ __forceinline__ void lds_write(const float2* v, void* lds, const StageDesc& st, int jt,
-                                          int TPP, int w, int W, int PR) {
+                                          int TPP, int w, int W, int PR, int off) {
 #pragma unroll
   for (int q = 0; q < P / R; ++q) {
-    const BfGeom g = geom(st, jt + TPP * q);
+    const BfGeom g = geom(st, start_bf(st, jt + TPP * q, off));
     for_lds<R, COLS>(g.out0, g.out_step, w, W, PR, [&](int i, int e) {
       if constexpr (PART == 0)
         static_cast<float2*>(lds)[e] = v[q * R + i];
@@ -347,11 +370,13 @@ __device__ __forceinline__ Pencil pencil_at(const PassDesc& p, long long pen, co
 // neighbouring threads on neighbouring rows, each row turned by the position
 // of its neighbour, so that a wave writes runs of W elements.  The change of
 // thread order rides on the last LDS exchange and the turn on the twiddles,
-// so neither costs anything.  Column tiles only reorder their own columns.  The rows' LDS pitch is 32 / W elements modulo
+// so neither costs anything.  Column tiles only reorder their own columns; on
+// the input side of a first pass the turn costs one product per value.  The rows' LDS pitch is 32 / W elements modulo
 // 32 then, which spreads those reads over all banks.
 constexpr int kTilePad = 33;
 
-template <int P, bool COLS, bool SPLIT, int MIN, int MOUT>
+// TURN: the input side may have a chain (column tiles).
+template <int P, bool COLS, bool SPLIT, int MIN, int MOUT, bool TURN>
 __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int tid,
                                           const float2* __restrict__ in,
                                           float2* __restrict__ out, void* lds) {
@@ -369,18 +394,25 @@ __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int
   const int PR = phys(L) + (turn && L >= 512 ? 32 / W : 0);
   const int2* chain = !COLS && MOUT == MAP_NATURAL ? p.out.chain : nullptr;
   int off = -1, unused = -1;   // position offset of the last stage (-1: none)
-  int off_cols = -1;
-  if (COLS && MOUT == MAP_NATURAL && p.out.chain) {
-    const int2 c = p.out.chain[w];
+  static_assert(!TURN || (COLS && MIN == MAP_NATURAL && MOUT != MAP_NATURAL), "first pass");
+  int off_cols = -1, off_in = -1;
+  if (COLS && MOUT == MAP_NATURAL) {
+    if (p.out.chain) {
+      const int2 c = p.out.chain[w];
+      w = c.x;
+      off_cols = c.y;
+    }
+  } else if (TURN && p.in.chain) {
+    const int2 c = p.in.chain[w];
     w = c.x;
-    off_cols = c.y;
+    off_in = c.y;
   }
   Pencil pc = pencil_at(p, tile * W + w, chain, unused);
   float2 v[P];
   {
     Addr<MIN> A;
     addr_init<MIN>(A, p.in, in, pc, L, S);
-    LFFT_RADIX_SWITCH(p.st[0].radix, (load_first<P, RR, MIN>(v, p, A, jt, TPP, pc.active)));
+    LFFT_RADIX_SWITCH(p.st[0].radix, (load_first<P, RR, MIN>(v, p, A, jt, TPP, pc.active, off_in)));
   }
   float2 twb[8];
   if (p.st[0].Ns > 1)
@@ -388,6 +420,9 @@ __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int
   for (int si = 0; si < p.nst; ++si) {
     const StageDesc& st = p.st[si];
     LFFT_RADIX_SWITCH(st.radix, (compute_stage<P, RR>(v, twb, p.sign, st.Ns > 1)));
+    if constexpr (TURN)
+      if (si == 0 && p.in.chain)
+        LFFT_RADIX_SWITCH(st.radix, (start_turn<P, RR>(v, st, p.sign, jt, TPP, off_in)));
     if (si + 1 < p.nst) {
       const StageDesc& nx = p.st[si + 1];
       const int w0 = w, j0 = jt;
@@ -399,16 +434,16 @@ __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int
       }
       if (nx.Ns > 1) LFFT_RADIX_SWITCH(nx.radix, (prefetch_tw<P, RR>(twb, nx, jt, TPP, off)));
       if constexpr (!SPLIT) {
-        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 0>(v, lds, st, j0, TPP, w0, W, PR)));
+        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 0>(v, lds, st, j0, TPP, w0, W, PR, si ? -1 : off_in)));
         __syncthreads();
         LFFT_RADIX_SWITCH(nx.radix, (lds_read<P, RR, COLS, 0>(v, lds, nx, jt, TPP, w, W, PR, off)));
         __syncthreads();
       } else {
-        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 1>(v, lds, st, j0, TPP, w0, W, PR)));
+        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 1>(v, lds, st, j0, TPP, w0, W, PR, si ? -1 : off_in)));
         __syncthreads();
         LFFT_RADIX_SWITCH(nx.radix, (lds_read<P, RR, COLS, 1>(v, lds, nx, jt, TPP, w, W, PR, off)));
         __syncthreads();
-        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 2>(v, lds, st, j0, TPP, w0, W, PR)));
+        LFFT_RADIX_SWITCH(st.radix, (lds_write<P, RR, COLS, 2>(v, lds, st, j0, TPP, w0, W, PR, si ? -1 : off_in)));
         __syncthreads();
         LFFT_RADIX_SWITCH(nx.radix, (lds_read<P, RR, COLS, 2>(v, lds, nx, jt, TPP, w, W, PR, off)));
         __syncthreads();

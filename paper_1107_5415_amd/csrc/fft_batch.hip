@@ -49,19 +49,19 @@ __global__ void __launch_bounds__(512) fft_batch_kernel(const BatchPass* __restr
     float2* dst = (bp.out_buf == 1 ? out : ws) + bp.out_off;
     switch (bp.variant) {
       case BATCH_ROWS_NN:
-        fastk::fast_tile<16, false, false, MAP_NATURAL, MAP_NATURAL>(bp.pd, tile, tid, src, dst, lds_raw);
+        fastk::fast_tile<16, false, false, MAP_NATURAL, MAP_NATURAL, false>(bp.pd, tile, tid, src, dst, lds_raw);
         break;
       case BATCH_ROWS_NI:
-        fastk::fast_tile<16, false, false, MAP_NATURAL, MAP_IDENTITY>(bp.pd, tile, tid, src, dst, lds_raw);
+        fastk::fast_tile<16, false, false, MAP_NATURAL, MAP_IDENTITY, false>(bp.pd, tile, tid, src, dst, lds_raw);
         break;
       case BATCH_COLS_NI:
-        fastk::fast_tile<16, true, false, MAP_NATURAL, MAP_IDENTITY>(bp.pd, tile, tid, src, dst, lds_raw);
+        fastk::fast_tile<16, true, false, MAP_NATURAL, MAP_IDENTITY, true>(bp.pd, tile, tid, src, dst, lds_raw);
         break;
       case BATCH_ROWS_IN:
-        fastk::fast_tile<16, false, false, MAP_IDENTITY, MAP_NATURAL>(bp.pd, tile, tid, src, dst, lds_raw);
+        fastk::fast_tile<16, false, false, MAP_IDENTITY, MAP_NATURAL, false>(bp.pd, tile, tid, src, dst, lds_raw);
         break;
       default:
-        fastk::fast_tile<16, true, false, MAP_IDENTITY, MAP_NATURAL>(bp.pd, tile, tid, src, dst, lds_raw);
+        fastk::fast_tile<16, true, false, MAP_IDENTITY, MAP_NATURAL, false>(bp.pd, tile, tid, src, dst, lds_raw);
         break;
     }
     // (a tile ends with a barrier after its last LDS read, so the next one

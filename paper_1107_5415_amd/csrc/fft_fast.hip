@@ -24,18 +24,18 @@ namespace lfft {
 namespace {
 using namespace dev;
 
-template <int P, bool COLS, bool SPLIT, int MIN, int MOUT>
+template <int P, bool COLS, bool SPLIT, int MIN, int MOUT, bool TURN>
 __global__ void __launch_bounds__(1024) fft_fast_kernel(PassDesc p, const float2* __restrict__ in,
                                                         float2* __restrict__ out) {
   extern __shared__ float2 lds_raw[];
   touch_args<sizeof(PassDesc)>();
-  fastk::fast_tile<P, COLS, SPLIT, MIN, MOUT>(p, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x, in,
+  fastk::fast_tile<P, COLS, SPLIT, MIN, MOUT, TURN>(p, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x, in,
                                               out, lds_raw);
 }
 
-template <int P, bool COLS, bool SPLIT, int MIN, int MOUT>
+template <int P, bool COLS, bool SPLIT, int MIN, int MOUT, bool TURN>
 hipError_t launch_t(const PassDesc& p, const float2* in, float2* out, hipStream_t s) {
-  auto k = fft_fast_kernel<P, COLS, SPLIT, MIN, MOUT>;
+  auto k = fft_fast_kernel<P, COLS, SPLIT, MIN, MOUT, TURN>;
   // set once; threads that race here all write the same attribute
   static std::atomic<bool> attr{false};
   if (!attr.load(std::memory_order_acquire)) {
@@ -56,9 +56,12 @@ hipError_t launch_t(const PassDesc& p, const float2* in, float2* out, hipStream_
 template <int P, bool COLS, bool SPLIT, int MIN>
 hipError_t launch_out(const PassDesc& p, const float2* in, float2* out, hipStream_t s) {
   switch (p.out.mode) {
-    case MAP_IDENTITY: return launch_t<P, COLS, SPLIT, MIN, MAP_IDENTITY>(p, in, out, s);
-    case MAP_LINEAR: return launch_t<P, COLS, SPLIT, MIN, MAP_LINEAR>(p, in, out, s);
-    default: return launch_t<P, COLS, SPLIT, MIN, MAP_NATURAL>(p, in, out, s);
+    case MAP_IDENTITY:
+      if constexpr (COLS && MIN == MAP_NATURAL)
+        if (p.in.chain) return launch_t<P, COLS, SPLIT, MIN, MAP_IDENTITY, true>(p, in, out, s);
+      return launch_t<P, COLS, SPLIT, MIN, MAP_IDENTITY, false>(p, in, out, s);
+    case MAP_LINEAR: return launch_t<P, COLS, SPLIT, MIN, MAP_LINEAR, false>(p, in, out, s);
+    default: return launch_t<P, COLS, SPLIT, MIN, MAP_NATURAL, false>(p, in, out, s);
   }
 }
 
@@ -72,8 +75,9 @@ hipError_t launch_in(const PassDesc& p, const float2* in, float2* out, hipStream
 
 const char* fast_kernel_name(const PassDesc& p) {
   const int min = p.in.mode == MAP_NATURAL ? 2 : 0;
-  return kernel_name_intern("fft_fast_kernel<16, %s, %s, %d, %d>", p.S > 1 ? "true" : "false",
-                            p.split ? "true" : "false", min, p.out.mode);
+  const bool turn = p.S > 1 && min == 2 && p.out.mode == MAP_IDENTITY && p.in.chain;
+  return kernel_name_intern("fft_fast_kernel<16, %s, %s, %d, %d, %s>", p.S > 1 ? "true" : "false",
+                            p.split ? "true" : "false", min, p.out.mode, turn ? "true" : "false");
 }
 
 hipError_t launch_fast_pass(const PassDesc& p, const float2* in, float2* out, hipStream_t s) {

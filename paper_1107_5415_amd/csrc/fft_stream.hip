@@ -164,14 +164,14 @@ __device__ __forceinline__ TileId tile_of(long long tile, int O, int S) {
 // loads of the first stage's inputs of one tile into v
 template <int L, bool COLS, int MIN>
 __device__ __forceinline__ void load_tile(float2* v, const PassDesc& p, const float2* __restrict__ in,
-                                          const TileId& t, int w, int jt) {
+                                          const TileId& t, int w, int jt, int off) {
   constexpr int R = StageR<L, 0>::value;
   constexpr int TPP = L / kP;
   Side<MIN> A;
   side_init<MIN>(A, p.in, in, t.b, COLS ? t.o0 : t.o0 + w, COLS ? t.s0 + w : t.s0, L, p.S);
 #pragma unroll
   for (int q = 0; q < kP / R; ++q) {
-    const int j = jt + TPP * q;
+    const int j = (jt + TPP * q + off) & (L - 1);
     side_positions<MIN, R>(A, p.in, p.S, j, L / R,
                            [&](int i, int off) {
                              // rows passes: non-temporal loads of the
@@ -195,6 +195,15 @@ __device__ __forceinline__ void load_tile(float2* v, const PassDesc& p, const fl
 template <int L, int SI>
 __device__ __forceinline__ int turned(int j, int off) {
   return SI + 1 == NStages<L>::value ? (j + off) & (L - 1) : j;
+}
+
+// The first stage likewise, on its inputs: with p = (j + off) mod L in the
+// place of j, value i is input (i + k) mod R of butterfly p mod (L / R),
+// k = p / (L / R), and output m carries the factor w^(-k m), w = exp(sign
+// 2 pi i / R), which start_turn takes off.
+template <int L>
+__device__ __forceinline__ int start_bf(int j, int off) {
+  return (j + off) & (L / StageR<L, 0>::value - 1);
 }
 
 template <int L, int SI>
@@ -259,6 +268,20 @@ __device__ __forceinline__ void stage_compute(float2* v, const float2* twb, int 
   }
 }
 
+template <int L>
+__device__ __forceinline__ void start_turn(float2* v, const PassDesc& p, int jt, int off) {
+  constexpr int R = StageR<L, 0>::value, T = L / R, LG = Lg<R>::value, TPP = L / kP;
+  const float2* tw = p.st[0].tw;   // exp(-2 pi i k / L)
+#pragma unroll
+  for (int q = 0; q < kP / R; ++q) {
+    const int kT = (jt + TPP * q + off) & (L - T);   // k L / R, k < R
+    float2 b[LG];
+#pragma unroll
+    for (int i = 0; i < LG; ++i) b[i] = tw[(kT << i) & (L - 1)];
+    apply_tw_s<R>(v + q * R, b, p.sign);
+  }
+}
+
 template <bool COLS, int L, int W>
 __device__ __forceinline__ int slds(int l, int w) {
   return sphys(COLS ? l * W + w : w * L + l);
@@ -275,7 +298,7 @@ __device__ __forceinline__ int slds_off(int base_e, int delta) {
 
 // write stage SI outputs, read stage SI+1 inputs
 template <int L, int W, bool COLS, int SI>
-__device__ __forceinline__ void exch_write(const float2* v, float2* lds, int jt, int w) {
+__device__ __forceinline__ void exch_write(const float2* v, float2* lds, int jt, int w, int off0) {
   constexpr int R = StageR<L, SI>::value;
   constexpr int Ns = StageNs<L, SI>::value;
   constexpr int TPP = L / kP;
@@ -284,7 +307,7 @@ __device__ __forceinline__ void exch_write(const float2* v, float2* lds, int jt,
   constexpr bool lin = COLS ? ((Ns * W) % 16 == 0) : (Ns % 16 == 0 || (Ns == 1 && R % 16 == 0));
 #pragma unroll
   for (int q = 0; q < kP / R; ++q) {
-    const int j = jt + TPP * q;
+    const int j = SI == 0 ? start_bf<L>(jt + TPP * q, off0) : jt + TPP * q;
     const int out0 = (j / Ns) * Ns * R + (j & (Ns - 1));
     const int eb = slds<COLS, L, W>(out0, w);
 #pragma unroll
@@ -312,18 +335,20 @@ __device__ __forceinline__ void exch_read(float2* v, const float2* lds, int jt, 
   }
 }
 
-template <int L, int W, bool COLS, int SI>
+template <int L, int W, bool COLS, bool TURN, int SI>
 __device__ __forceinline__ void stages_from(float2* v, float2* twb, float2* lds, const PassDesc& p,
-                                            int jt, int w, int off) {
+                                            int jt, int w, int off0, int off) {
   constexpr int NS = NStages<L>::value;
   stage_compute<L, SI>(v, twb, p.sign);
+  if constexpr (COLS && SI == 0 && TURN)
+    if (p.in.chain) start_turn<L>(v, p, jt, off0);
   if constexpr (SI + 1 < NS) {
     tw_load<L, SI + 1>(twb, p, jt, off);
-    exch_write<L, W, COLS, SI>(v, lds, jt, w);
+    exch_write<L, W, COLS, SI>(v, lds, jt, w, off0);
     __syncthreads();
     exch_read<L, W, COLS, SI + 1>(v, lds, jt, w, off);
     __syncthreads();
-    stages_from<L, W, COLS, SI + 1>(v, twb, lds, p, jt, w, off);
+    stages_from<L, W, COLS, TURN, SI + 1>(v, twb, lds, p, jt, w, off0, off);
   }
 }
 
@@ -380,12 +405,18 @@ __global__ void __launch_bounds__(W* L / kP, kWavesPerSimd)
   const int jt = COLS ? tid / W : tid % TPP;
   // columns in the order of natural neighbours (MapDesc::chain): the lanes of
   // a tile row still read the same segment, and they write runs
-  int off = 0;
+  int off = 0, off0 = 0;
   if constexpr (COLS && MOUT == MAP_NATURAL) {
     if (p.out.chain) {
       const int2 c = p.out.chain[w];
       w = c.x;
       off = c.y;
+    }
+  } else if constexpr (COLS && MIN == MAP_NATURAL) {
+    if (p.in.chain) {
+      const int2 c = p.in.chain[w];
+      w = c.x;
+      off0 = c.y;
     }
   }
   const long long npen = p.batch * (long long)p.O * p.S;
@@ -405,8 +436,9 @@ __global__ void __launch_bounds__(W* L / kP, kWavesPerSimd)
   float2 va[kP];
   for (; tile < end; tile += nwg_x) {
     const TileId ta = tile_of<W>(tile, p.O, p.S);
-    load_tile<L, COLS, MIN>(va, p, in, ta, w, jt);
-    stages_from<L, W, COLS, 0>(va, twb, lds, p, jt, w, off);
+    load_tile<L, COLS, MIN>(va, p, in, ta, w, jt, off0);
+    stages_from<L, W, COLS, MIN == MAP_NATURAL && MOUT != MAP_NATURAL, 0>(va, twb, lds, p, jt, w,
+                                                                         off0, off);
     store_tile<L, COLS, POST, MOUT>(va, p, out, ta, w, jt, off);
   }
 }

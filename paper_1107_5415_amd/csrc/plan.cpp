@@ -492,26 +492,38 @@ std::vector<int2> row_chains(const Side& side, const std::vector<i64>& eps,
   return out;
 }
 
-// The W columns of a tile of the last pass (the digit a whole, others after
-// it) in runs of natural neighbours, see MapDesc::chain: the step to the next
-// natural index moves c columns and a fixed number of positions.  Empty
-// unless 0 < |c| < W.
+// The W columns of a tile of a first or last pass over the digit a in runs of
+// natural neighbours on `side`, see MapDesc::chain: the step to the next
+// natural index moves c columns and a fixed number of positions.  The columns
+// are whole axes after the digit's, or (input side) the low digit of its own
+// axis.  Empty unless 0 < |c| < W, and where the order would stay as it is.
 std::vector<int2> column_chain(const Side& side, const std::vector<i64>& eps,
                                const std::vector<Digit>& dg, int a, int W) {
-  const int D = (int)dg.size(), end = dg[D - 1].axis;
-  if (dg[a].part != 0 || dg[D - 1].part != 0) return {};
+  const int D = (int)dg.size(), axis = dg[a].axis, end = dg[D - 1].axis;
   for (size_t t = 0; t < eps.size(); ++t)
-    if ((int)t != dg[a].axis && (int)t != end && side.next[t] != 0) return {};
-  i64 c = side.next[end];
-  if (2 * c > eps[end]) c -= eps[end];
+    if ((int)t != axis && (int)t != end && side.next[t] != 0) return {};
+  i64 c = 0, step = 0;   // columns and positions per natural step
+  if (dg[a].part == 0 && dg[D - 1].part == 0 && axis != end) {
+    step = side.next[axis];
+    c = side.next[end];
+    if (2 * c > eps[end]) c -= eps[end];
+  } else if (dg[a].part == 1 && dg[D - 1].part == 2 && a + 2 == D && axis == end) {
+    const i64 lo = dg[D - 1].n;
+    step = side.next[axis] / lo;
+    c = side.next[axis] % lo;
+    if (2 * c > lo) {
+      c -= lo;
+      ++step;
+    }
+  }
+  step = posmod(step, dg[a].n);
   const i64 k = c < 0 ? -c : c;
-  if (k == 0 || k >= W) return {};
+  if (k == 0 || k >= W || (c == 1 && step == 0)) return {};
   std::vector<int2> out;
   for (i64 r = 0; r < k; ++r) {
     const i64 n = (W - r + k - 1) / k;   // columns r, r + k, ...
     for (i64 i = 0; i < n; ++i)
-      out.push_back(make_int2((int)(r + k * (c > 0 ? i : n - 1 - i)),
-                              (int)((i * side.next[dg[a].axis]) % dg[a].n)));
+      out.push_back(make_int2((int)(r + k * (c > 0 ? i : n - 1 - i)), (int)((i * step) % dg[a].n)));
   }
   return out;
 }
@@ -790,7 +802,12 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
   }
   if ((end.kind == 1 || end.kind == 2) && end.S > 1 && R1.b - R1.a == 1 && !end.post) {
     const std::vector<int2> chain = column_chain(out_side, p->eps, dg, R1.a, end.W);
-    if (!chain.empty()) E.out_nat.chain = p->blob.ref(chain);
+    if (!chain.empty() && dg[R1.a].part == 0) E.out_nat.chain = p->blob.ref(chain);
+  }
+  const PassDesc& begin = E.passes.front();
+  if (np > 1 && (begin.kind == 1 || begin.kind == 2) && begin.S > 1 && R0.b - R0.a == 1) {
+    const std::vector<int2> chain = column_chain(in_side, p->eps, dg, R0.a, begin.W);
+    if (!chain.empty()) E.in_nat.chain = p->blob.ref(chain);
   }
 }
 

@@ -93,9 +93,9 @@ __device__ __forceinline__ float re_dot(float2 g, float2 x) { return g.x * x.x +
 
 // The adjoints with mask gradients do both in one pass over the incoming
 // gradients, which the two need alike: 24 bytes a point instead of 32.  Bound
-// by HBM; 16 signals, levels of 2^20 .. 2^17 points: split's adjoint and mask
-// gradient 26.6 + 25.4 us a level as two kernels (three levels of the four are
-// 35.6 us as one; the unsplit's 27.7 + 30.8, 37.9 us.
+// by HBM.  16 signals, four levels from 2^20 points, mean of a level: split's
+// adjoint and mask gradient 26.6 + 25.4 us as two kernels, 35.6 us as one; the
+// unsplit's 27.7 + 30.8, 37.9 us.
 //
 // Adjoint of the split (the unsplit of g1, g2 into ga) and the gradient of its
 // mask, from its input ah.
