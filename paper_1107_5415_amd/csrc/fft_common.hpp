@@ -256,6 +256,15 @@ __device__ __forceinline__ void touch_args() {
   asm volatile("" ::"s"(acc));
 }
 
+// The kernel's first argument in place.  A by-value descriptor whose input and
+// output maps meet in one address (kernels with both sides natural) would be
+// copied to scratch memory, 1.4 KB per thread.
+template <class T>
+__device__ __forceinline__ const T& first_arg() {
+  typedef const __attribute__((address_space(4))) T* Arg;
+  return *(const T*)(Arg)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 // Non-temporal 8-byte load and store: the line is not kept for reuse.  For
 // data read or written once by a call (whole lines, so that no other wave
 // has to fetch the same line again), which leaves the caches to the data

@@ -25,10 +25,11 @@ namespace {
 using namespace dev;
 
 template <int P, bool COLS, bool SPLIT, int MIN, int MOUT, bool TURN>
-__global__ void __launch_bounds__(1024) fft_fast_kernel(PassDesc p, const float2* __restrict__ in,
+__global__ void __launch_bounds__(1024) fft_fast_kernel(PassDesc, const float2* __restrict__ in,
                                                         float2* __restrict__ out) {
   extern __shared__ float2 lds_raw[];
   touch_args<sizeof(PassDesc)>();
+  const PassDesc& p = first_arg<PassDesc>();
   fastk::fast_tile<P, COLS, SPLIT, MIN, MOUT, TURN>(p, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x, in,
                                               out, lds_raw);
 }
