@@ -162,21 +162,6 @@ __device__ __forceinline__ void group_add(const MapDesc& m, long long* c, int4 b
   }
 }
 
-__device__ __forceinline__ long long map_index(const MapDesc& m, long long b, int o, int l, int s,
-                                               int L, int S) {
-  if (m.mode == MAP_IDENTITY) return b * m.bstride + ((long long)o * L + l) * (long long)S + s;
-  if (m.mode == MAP_LINEAR)
-    return b * m.bstride + (long long)m.To[o].x + (long long)m.Tl[l].x + (long long)m.Ts[s].x;
-  long long c[4] = {0, 0, 0, 0};
-  group_add(m, c, m.To[o]);
-  group_add(m, c, m.Tl[l]);
-  group_add(m, c, m.Ts[s]);
-  long long idx = b * m.bstride;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) idx += c[i] * m.box_stride[i];
-  return idx;
-}
-
 }  // namespace dev
 }  // namespace lfft
 
@@ -184,7 +169,7 @@ namespace lfft {
 namespace dev {
 
 // Group sum in Z^d / H Z^d of two reduced coordinate vectors (int32; the
-// planner routes lattices with m >= 2^30 to the generic kernel).
+// planner routes lattices with m >= 2^30 to the mixed-radix kernel).
 __device__ __forceinline__ void gadd32(const MapDesc& m, int* c, int4 b) {
   c[0] += b.x;
   c[1] += b.y;
