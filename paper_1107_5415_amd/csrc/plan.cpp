@@ -519,6 +519,17 @@ std::pair<i64, i64> chain_step(const Side& side, const std::vector<i64>& eps,
   return {c, posmod(step, dg[a].n)};
 }
 
+// A pass over [a, b) = whole axes and the high digit of the last one: the 16
+// natural neighbours of a line of `side` lie in 16 groups of columns, at least
+// 16 columns apart.
+bool lines_apart(const Side& side, const std::vector<Digit>& dg, int a, int b) {
+  const int D = (int)dg.size();
+  if (b - a < 2 || b + 1 != D || dg[b - 1].part != 1 || dg[b].part != 2) return false;
+  const i64 lo = dg[b].n, c = side.next[dg[b].axis] % lo;
+  const i64 g = gcd64(c, lo);
+  return g >= 16 && lo / g >= 16;
+}
+
 // The W columns of a tile of a first or last pass over the digit a in runs of
 // natural neighbours on `side`, see MapDesc::chain.  Empty unless they lie
 // 0 < |c| < W columns apart, and where the order would stay as it is.
@@ -693,8 +704,18 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
         if (np > 1 && pi == np - 1) k = chain_step(out_side, p->eps, dg, R.a, R.b).first;
         int Wc = (k < 0 ? -k : k) > 4 ? 256 : 64;
         while (Wc > 1 && (pd.S % Wc != 0 || (i64)Wc * pd.L > 16384)) Wc /= 2;
-        while (Wc > 8 && R.b - R.a > 1 && (i64)Wc * pd.L > 8192) Wc /= 2;
-        while (Wc > 8 && npen / Wc < 512) Wc /= 2;
+        // A four-step first pass whose input lines of 16 neighbours lie in 16
+        // different tiles: full tiles, all of them in flight together, where
+        // the input is larger than the L2s (32 MB).  Inverse of [[2048, k],
+        // [0, 2048]], 8 / 16 columns: k = 8, 16, 32 76 / 67, 84 / 70, 87 / 79
+        // us; in fewer tiles (k = 2) 57 / 63, with neighbours in one tile
+        // (forward, k = 8) 48.5 / 54, with 2 x 2^21 points 61 / 63.
+        const bool spread = np > 1 && pi == 0 && p->m >= (i64(1) << 22) &&
+                            lines_apart(in_side, dg, R.a, R.b);
+        if (!spread) {
+          while (Wc > 8 && R.b - R.a > 1 && (i64)Wc * pd.L > 8192) Wc /= 2;
+        }
+        while (Wc > 8 && npen / Wc < (spread ? 256 : 512)) Wc /= 2;
         pd.W = Wc;
         pd.P = 16;
         pd.split = ((i64)Wc * pd.L * 17 / 16 * 8 > 72 * 1024) ? 1 : 0;
@@ -944,7 +965,13 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
           // kernels.  Not beyond the streaming kernels' 2^28 bound, where the
           // wider low digit measured faster overall.
           if (is_pow2(n) && n >= 32 * 32 && p->m < (i64(1) << 28)) {
-            const i64 rows = p->m >= (i64(1) << 22) ? 4096 : 2048;
+            // Rows of 8192 where those of 4096 would leave the high digit and
+            // the short axes before it 2048 points, eight to a tile, instead
+            // of 1024 in wider tiles: [[2048, 2], [0, 4096]] 151 / 116 us,
+            // inverse of [[4096, 32], [0, 2048]] 241 / 199.
+            i64 rows = p->m >= (i64(1) << 22) ? 4096 : 2048, lead = 1;
+            for (auto& g : p->digits) lead *= g.n;
+            if (rows == 4096 && lead > 1 && lead * (n / rows) == 2048 && n / 8192 >= 32) rows = 8192;
             if (n / rows <= kMaxPencil) lo = std::min(lo, rows);
             if (n / lo < 32) lo = n / 32;
           }

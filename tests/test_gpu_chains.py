@@ -38,6 +38,15 @@ CASES = [
     ("three_axes_a_pass_each", ((64, 16, 0), (0, 64, 16), (0, 0, 64)), 1, None),
     ("three_axes_long", ((256, 64, 0), (0, 256, 64), (0, 0, 64)), 1, None),
     ("streaming_columns_2^20", ((1024, 256), (0, 1024)), 2, ("stores", "loads")),
+    ("full_tiles_of_spread_lines", ((2048, 16), (0, 2048)), 1, None),
+    ("rows_8192_after_short_axis", ((4096, 32), (0, 2048)), 1, None),
+]
+# M, what the plan log says of the first pass (forward, inverse) and the last
+TILES = [
+    (((2048, 16), (0, 2048)), "pencil 1024 x 8 ", "pencil 1024 x 16 ", "pencil 4096 x 4 "),
+    (((2048, 2), (0, 2048)), "pencil 1024 x 8 ", "pencil 1024 x 8 ", "pencil 4096 x 4 "),
+    (((4096, 32), (0, 2048)), "pencil 1024 x 8 ", "pencil 1024 x 16 ", "pencil 8192 x 2 "),
+    (((1024, 16), (0, 2048)), "pencil 1024 x 8 ", "pencil 1024 x 8 ", "pencil 2048 x 4 "),
 ]
 LOGGED = [c for c in CASES if c[3]]
 
@@ -53,6 +62,19 @@ def test_rule_applies(name, M, batch, log):
     for side, want in zip(("forward", "inverse"), log):
         lines = [l for l in r.stderr.splitlines() if "  " + side in l]
         assert lines and any(want + " in natural runs" in l for l in lines), r.stderr
+
+
+@pytest.mark.parametrize("M,fwd,inv,last", TILES)
+def test_tiles_of_a_short_axis_and_a_long_one(M, fwd, inv, last):
+    """(CPU) Tile width of the first pass and rows of the last."""
+    code = ("import sys; sys.path.insert(0, %r); from paper_1107_5415_amd import lfft; "
+            "lfft.LatticePlan(%r, host_only=True)" % (ROOT, M))
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True,
+                       env=dict(os.environ, LFFT_LOG="1"))
+    assert r.returncode == 0, r.stderr
+    for side, want in (("forward", fwd), ("inverse", inv)):
+        lines = [l for l in r.stderr.splitlines() if "  " + side in l]
+        assert want in lines[0] and last in lines[1], r.stderr
 
 
 def _rel(a, b):
