@@ -62,8 +62,7 @@ __device__ __forceinline__ BfGeom geom_turned(const StageDesc& st, int bl, int o
 
 // First stage of a one-digit pencil, butterfly `bl` turned by `off` positions
 // on its inputs: with p = (bl + off) mod L value i is input (i + k) mod R of
-// butterfly p mod (L / R), k = p / (L / R); its output m carries the factor
-// w^(-k m), w = exp(sign 2 pi i / R), which start_turn takes off.
+// butterfly p mod (L / R), k = p / (L / R); load_first puts the inputs in order.
 __device__ __forceinline__ int start_bf(const StageDesc& st, int bl, int off) {
   return off < 0 ? bl : (bl + off) & ((st.n >> st.lg_r) - 1);
 }
@@ -148,7 +147,7 @@ __device__ __forceinline__ void dftR(float2* v, int sign) {
   dft_pow2<R>(v, sign);
 }
 
-template <int P, int R, int MIN>
+template <int P, int R, int MIN, bool TURN>
 __device__ __forceinline__ void load_first(float2* v, const PassDesc& p, const Addr<MIN>& A,
                                            int jt, int TPP, bool active, int off) {
   const StageDesc& st = p.st[0];
@@ -164,6 +163,12 @@ __device__ __forceinline__ void load_first(float2* v, const PassDesc& p, const A
       for (int i = 0; i < R; ++i) v[q * R + i] = make_float2(0.f, 0.f);
     }
   }
+  if constexpr (TURN)
+    if (off >= 0) {
+#pragma unroll
+      for (int q = 0; q < P / R; ++q)
+        rotate_by<R>(&v[q * R], ((jt + TPP * q + off) & (st.n - 1)) >> (st.lg_n - st.lg_r));
+    }
 }
 
 // Base twiddles of a stage: for every butterfly of the thread, w^(2^k) for
@@ -214,20 +219,6 @@ __device__ __forceinline__ void apply_tw(float2* x, const float2* b, int sign) {
   }
 #pragma unroll
   for (int i = 1; i < R; ++i) x[i] = c_mul(x[i], pw[i]);
-}
-
-template <int P, int R>
-__device__ __forceinline__ void start_turn(float2* v, const StageDesc& st, int sign, int jt,
-                                           int TPP, int off) {
-  constexpr int LG = R == 16 ? 4 : R == 8 ? 3 : R == 4 ? 2 : 1;
-#pragma unroll
-  for (int q = 0; q < P / R; ++q) {
-    const int kT = (jt + TPP * q + off) & (st.n - (st.n >> st.lg_r));   // k L / R, k < R
-    float2 b[LG];
-#pragma unroll
-    for (int i = 0; i < LG; ++i) b[i] = st.tw[(kT << i) & (st.n - 1)];
-    apply_tw<R>(&v[q * R], b, sign);
-  }
 }
 
 // tw: the stage has twiddles (Ns > 1; the first stage of a digit has none)
@@ -371,8 +362,11 @@ __device__ __forceinline__ Pencil pencil_at(const PassDesc& p, long long pen, co
 // of its neighbour, so that a wave writes runs of W elements.  The change of
 // thread order rides on the last LDS exchange and the turn on the twiddles,
 // so neither costs anything.  Column tiles only reorder their own columns; on
-// the input side of a first pass the turn costs one product per value.  The rows' LDS pitch is 32 / W elements modulo
-// 32 then, which spreads those reads over all banks.
+// the input side of a first pass the turn costs log2(R) selects per value and,
+// unlike a product with the root that the turn leaves on the outputs, no
+// rounding (mask gradients of 16 x 2^20 points were up to 8% further from 64
+// bits with it).  The rows' LDS pitch is 32 / W elements modulo 32 then, which
+// spreads those reads over all banks.
 constexpr int kTilePad = 33;
 
 // TURN: the input side may have a chain (column tiles).
@@ -412,7 +406,7 @@ __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int
   {
     Addr<MIN> A;
     addr_init<MIN>(A, p.in, in, pc, L, S);
-    LFFT_RADIX_SWITCH(p.st[0].radix, (load_first<P, RR, MIN>(v, p, A, jt, TPP, pc.active, off_in)));
+    LFFT_RADIX_SWITCH(p.st[0].radix, (load_first<P, RR, MIN, TURN>(v, p, A, jt, TPP, pc.active, off_in)));
   }
   float2 twb[8];
   if (p.st[0].Ns > 1)
@@ -420,9 +414,6 @@ __device__ __forceinline__ void fast_tile(const PassDesc& p, long long tile, int
   for (int si = 0; si < p.nst; ++si) {
     const StageDesc& st = p.st[si];
     LFFT_RADIX_SWITCH(st.radix, (compute_stage<P, RR>(v, twb, p.sign, st.Ns > 1)));
-    if constexpr (TURN)
-      if (si == 0 && p.in.chain)
-        LFFT_RADIX_SWITCH(st.radix, (start_turn<P, RR>(v, st, p.sign, jt, TPP, off_in)));
     if (si + 1 < p.nst) {
       const StageDesc& nx = p.st[si + 1];
       const int w0 = w, j0 = jt;

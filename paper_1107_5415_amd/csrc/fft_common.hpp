@@ -122,6 +122,27 @@ __device__ __forceinline__ void dft_pow2(float2* v, int sign) {
   Combine<R, 0>::run(v, e, o, sign);
 }
 
+// v[i] <- v[(i - k) mod R], 0 <= k < R, different in every lane: a select per
+// value and bit of k, and no rounding.  In place, one cycle after the other.
+template <int R, int S = 1>
+__device__ __forceinline__ void rotate_by(float2* v, int k) {
+  if constexpr (S < R) {
+    const bool on = (k & S) != 0;
+#pragma unroll
+    for (int r = 0; r < S; ++r) {
+      const float2 last = v[R - S + r];
+#pragma unroll
+      for (int i = R - S + r; i >= S; i -= S) {
+        v[i].x = on ? v[i - S].x : v[i].x;
+        v[i].y = on ? v[i - S].y : v[i].y;
+      }
+      v[r].x = on ? last.x : v[r].x;
+      v[r].y = on ? last.y : v[r].y;
+    }
+    rotate_by<R, 2 * S>(v, k);
+  }
+}
+
 __device__ __forceinline__ void dft3(float2* v, int sign) {
   const float h = 0.86602540378443864676f;  // sqrt(3)/2
   float2 t1 = c_add(v[1], v[2]);

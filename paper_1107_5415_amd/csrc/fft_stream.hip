@@ -199,8 +199,7 @@ __device__ __forceinline__ int turned(int j, int off) {
 
 // The first stage likewise, on its inputs: with p = (j + off) mod L in the
 // place of j, value i is input (i + k) mod R of butterfly p mod (L / R),
-// k = p / (L / R), and output m carries the factor w^(-k m), w = exp(sign
-// 2 pi i / R), which start_turn takes off.
+// k = p / (L / R), until start_turn puts the inputs in order.
 template <int L>
 __device__ __forceinline__ int start_bf(int j, int off) {
   return (j + off) & (L / StageR<L, 0>::value - 1);
@@ -269,17 +268,10 @@ __device__ __forceinline__ void stage_compute(float2* v, const float2* twb, int 
 }
 
 template <int L>
-__device__ __forceinline__ void start_turn(float2* v, const PassDesc& p, int jt, int off) {
-  constexpr int R = StageR<L, 0>::value, T = L / R, LG = Lg<R>::value, TPP = L / kP;
-  const float2* tw = p.st[0].tw;   // exp(-2 pi i k / L)
+__device__ __forceinline__ void start_turn(float2* v, int jt, int off) {
+  constexpr int R = StageR<L, 0>::value, T = L / R, TPP = L / kP;
 #pragma unroll
-  for (int q = 0; q < kP / R; ++q) {
-    const int kT = (jt + TPP * q + off) & (L - T);   // k L / R, k < R
-    float2 b[LG];
-#pragma unroll
-    for (int i = 0; i < LG; ++i) b[i] = tw[(kT << i) & (L - 1)];
-    apply_tw_s<R>(v + q * R, b, p.sign);
-  }
+  for (int q = 0; q < kP / R; ++q) rotate_by<R>(v + q * R, ((jt + TPP * q + off) & (L - 1)) / T);
 }
 
 template <bool COLS, int L, int W>
@@ -339,9 +331,9 @@ template <int L, int W, bool COLS, bool TURN, int SI>
 __device__ __forceinline__ void stages_from(float2* v, float2* twb, float2* lds, const PassDesc& p,
                                             int jt, int w, int off0, int off) {
   constexpr int NS = NStages<L>::value;
-  stage_compute<L, SI>(v, twb, p.sign);
   if constexpr (COLS && SI == 0 && TURN)
-    if (p.in.chain) start_turn<L>(v, p, jt, off0);
+    if (p.in.chain) start_turn<L>(v, jt, off0);
+  stage_compute<L, SI>(v, twb, p.sign);
   if constexpr (SI + 1 < NS) {
     tw_load<L, SI + 1>(twb, p, jt, off);
     exch_write<L, W, COLS, SI>(v, lds, jt, w, off0);
