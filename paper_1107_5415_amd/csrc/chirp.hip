@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(W* N / kV)
       if (l >= p.L) continue;
       float2 x = c_mul(v[i], chirp_at(p, l));
       if (p.post) x = c_mul(x, post_twiddle(p, (unsigned)l * lo));
-      dst[off[i]] = make_float2(x.x * p.scale, x.y * p.scale);
+      dst[off[i]] = c_scale(x, p.scale, p.scale_lo);
     }
   }
 }
@@ -267,7 +267,7 @@ __global__ void __launch_bounds__(W* H / kV)
       const long long l = l0 + (long long)i * T * Rw;
       if (l >= p.L) continue;
       const float2 x = c_mul(v[i], chirp_at(p, (int)l));
-      dst[off[i]] = make_float2(x.x * p.scale, x.y * p.scale);
+      dst[off[i]] = c_scale(x, p.scale, p.scale_lo);
     }
   }
 }
@@ -369,6 +369,12 @@ hipError_t launch_cols_h(const PassDesc& p, const float2* in, float2* out, hipSt
 }
 
 }  // namespace
+
+std::vector<int> chirp_radices(int N, bool second) {
+  std::vector<int> r;
+  for (int i = 0; i < stages(N); ++i) r.push_back(radix_at(N, second ? stages(N) - 1 - i : i));
+  return r;
+}
 
 const char* chirp_kernel_name(const PassDesc& p, int step) {
   if (p.kind == 5)

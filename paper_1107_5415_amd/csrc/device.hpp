@@ -89,7 +89,7 @@ struct PassDesc {
   int nst;
   StageDesc st[kMaxStages];
   int sign;                   // -1 forward, +1 inverse
-  float scale;                // applied when storing
+  float scale, scale_lo;      // applied when storing: their sum
   // streaming kernel, last pass of a natural-order transform whose rows
   // pencils write whole aligned rows of the caller's output: stores marked
   // non-temporal, so that they do not evict the input and the intermediate

@@ -4,55 +4,10 @@
 // rounded once.
 #pragma once
 #include "fft_common.hpp"
+#include "roots.hpp"
 
 namespace lfft {
 namespace dev {
-
-constexpr double kTwoPi = 6.283185307179586476925286766559;
-
-// Taylor series on |x| <= pi/4
-constexpr double sin_small(double x) {
-  double t = x, s = x;
-  for (int k = 1; k < 12; ++k) {
-    t *= -x * x / ((2 * k) * (2 * k + 1));
-    s += t;
-  }
-  return s;
-}
-constexpr double cos_small(double x) {
-  double t = 1, s = 1;
-  for (int k = 1; k < 12; ++k) {
-    t *= -x * x / ((2 * k - 1) * (2 * k));
-    s += t;
-  }
-  return s;
-}
-// cos and sin of 2 pi k / n, the angle reduced to an octant in integers
-constexpr double cos_frac(int k, int n) {
-  k %= n;
-  if (2 * k > n) k = n - k;                     // [0, pi]
-  if (4 * k > n) return -cos_frac(n - 2 * k, 2 * n);  // pi - x
-  if (8 * k > n) return sin_small(kTwoPi * (n - 4 * k) / (4.0 * n));
-  return cos_small(kTwoPi * k / n);
-}
-constexpr double sin_frac(int k, int n) {
-  k %= n;
-  if (2 * k > n) return -sin_frac(n - k, n);
-  if (4 * k > n) return sin_frac(n - 2 * k, 2 * n);
-  if (8 * k > n) return cos_small(kTwoPi * (n - 4 * k) / (4.0 * n));
-  return sin_small(kTwoPi * k / n);
-}
-
-template <int N>
-struct Roots {
-  float c[N] = {}, s[N] = {};
-  constexpr Roots() {
-    for (int k = 0; k < N; ++k) {
-      c[k] = (float)cos_frac(k, N);
-      s[k] = (float)sin_frac(k, N);
-    }
-  }
-};
 
 // f(k, X_k) for every output k of the DFT of odd length P, in pairs
 // (k, P - k): with a = x_0 + sum_j cos(2 pi jk/P) (x_j + x_{P-j}) and

@@ -304,22 +304,21 @@ __device__ __forceinline__ void store_last_r(const float2* v, const PassDesc& p,
                                              const Pencil& pc, int off0) {
   const StageDesc& st = p.st[p.nst - 1];
   float2* out = const_cast<float2*>(A.base);
-  const bool scaled = p.scale != 1.0f;
+  // (read once: for all the compiler knows, the stores below change them)
+  const float scale = p.scale, scale_lo = p.scale_lo;
+  const bool scaled = scale != 1.0f, post = p.post != 0;
   // four-step twiddle exponent (l mod post_lmod) * lo, lo fixed per pencil
-  const unsigned lo = p.post ? post_lo(p, pc.s) : 0u;
+  const unsigned lo = post ? post_lo(p, pc.s) : 0u;
 #pragma unroll
   for (int q = 0; q < P / R; ++q) {
     const BfGeom g = off0 < 0 ? geom(st, jt + TPP * q) : geom_turned(st, jt + TPP * q, off0);
     for_positions<MOUT, R>(A, p.out, p.S, g.out0, g.out_step, [&](int i, int off) {
       float2 x = v[q * R + i];
-      if (p.post) {
+      if (post) {
         const unsigned l = (unsigned)(g.out0 + i * g.out_step) & (unsigned)(p.post_lmod - 1);
         x = c_mul(x, post_twiddle(p, l * lo));
       }
-      if (scaled) {
-        x.x *= p.scale;
-        x.y *= p.scale;
-      }
+      if (scaled) x = c_scale(x, scale, scale_lo);
       out[(unsigned)off] = x;
     });
   }

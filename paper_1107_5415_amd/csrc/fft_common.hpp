@@ -19,6 +19,10 @@ __device__ __forceinline__ float2 c_conj(float2 a) { return make_float2(a.x, -a.
 __device__ __forceinline__ float2 c_muli(float2 a, int sign) {
   return sign < 0 ? make_float2(a.y, -a.x) : make_float2(-a.y, a.x);
 }
+// a (s + lo)
+__device__ __forceinline__ float2 c_scale(float2 a, float s, float lo) {
+  return make_float2(fmaf(a.x, s, a.x * lo), fmaf(a.y, s, a.y * lo));
+}
 __device__ __forceinline__ float2 tw_lookup(const float2* tw, long long k, int sign) {
   float2 w = tw[k];
   return sign < 0 ? w : c_conj(w);

@@ -305,9 +305,7 @@ __global__ void __launch_bounds__(kNT) fft_mfma_kernel(PassDesc p, const float2*
       if (p.sign > 0) tw.y = -tw.y;
       x = c_mul(x, tw);
     }
-    x.x *= p.scale;
-    x.y *= p.scale;
-    out[side_index<MOUT>(p.out, b, o, l, s, L, S)] = x;
+    out[side_index<MOUT>(p.out, b, o, l, s, L, S)] = c_scale(x, p.scale, p.scale_lo);
   }
 }
 

@@ -146,8 +146,9 @@ __device__ __forceinline__ void stage(PassArg arg, int si, const TileOf& t,
 #pragma unroll
         for (int i = 0; i < R; ++i) v[i] = c_mul(v[i], post_twiddle(p, x0 + (unsigned)i * xs));
       }
+      const float scale = p.scale, scale_lo = p.scale_lo;
 #pragma unroll
-      for (int i = 0; i < R; ++i) dst[off[i]] = make_float2(v[i].x * p.scale, v[i].y * p.scale);
+      for (int i = 0; i < R; ++i) dst[off[i]] = c_scale(v[i], scale, scale_lo);
     } else {
       const int e0 = out0 * p.ls + w * p.ws, es = out_step * p.ls;
       if constexpr (R > 16) {
@@ -288,7 +289,7 @@ __global__ void __launch_bounds__(kPassThreads)
     offsets<1, WIDE>(p, p.out, pc, (int)l, 0, off);
     float2 v = A[mphys((int)l * p.ls + w * p.ws)];
     if (p.post) v = c_mul(v, post_twiddle(p, post_pos(p, l) * post_lo(p, pc.s)));
-    out[pc.b * p.out.bstride + off[0]] = make_float2(v.x * p.scale, v.y * p.scale);
+    out[pc.b * p.out.bstride + off[0]] = c_scale(v, p.scale, p.scale_lo);
   }
 }
 

@@ -357,7 +357,7 @@ __device__ __forceinline__ void store_tile(const float2* v, const PassDesc& p,
   Side<MOUT> A;
   side_init<MOUT>(A, p.out, out, t.b, o, s, L, p.S);
   float2* base = const_cast<float2*>(A.base);
-  const bool scaled = p.scale != 1.0f;
+  const bool scaled = !POST && p.scale != 1.0f;
   const unsigned lo = POST ? post_lo(p, s) : 0u;
 #pragma unroll
   for (int q = 0; q < kP / R; ++q) {
@@ -365,11 +365,10 @@ __device__ __forceinline__ void store_tile(const float2* v, const PassDesc& p,
     side_positions<MOUT, R>(A, p.out, p.S, out0, Ns, [&](int i, int off) {
       float2 x = v[q * R + i];
       // (the pencil is one digit, the four-step axis's high one)
-      if constexpr (POST) x = c_mul(x, post_twiddle(p, (unsigned)(out0 + i * Ns) * lo));
-      if (scaled) {
-        x.x *= p.scale;
-        x.y *= p.scale;
-      }
+      if constexpr (POST)
+        x = c_mul(x, post_twiddle(p, (unsigned)(out0 + i * Ns) * lo));
+      else if (scaled)   // (only a call's last pass is)
+        x = c_scale(x, p.scale, p.scale_lo);
       if constexpr (MOUT == MAP_NATURAL && !COLS) {
         if (p.stream_out) {
           store_stream(base + (unsigned)off, x);
@@ -505,6 +504,12 @@ bool stream_supported(int L, int W, bool cols) {
   return (L == 4096 && W == 4) || (L == 2048 && W == 8) || (L == 1024 && (W == 16 || W == 8)) ||
          (L == 512 && (W == 32 || W == 16 || W == 8)) ||
          (L == 256 && (W == 64 || W == 32 || W == 16 || W == 8));
+}
+
+std::vector<int> stream_radices(int L) {
+  std::vector<int> r;
+  for (int i = 0; i < seq_len(L); ++i) r.push_back(seq_radix(L, i));
+  return r;
 }
 
 const char* stream_kernel_name(const PassDesc& p) {

@@ -3,6 +3,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include "device.hpp"
 
 namespace lfft {
@@ -94,6 +96,10 @@ hipError_t launch_chirp_tile(const PassDesc& p, const float2* in, float2* out, h
 hipError_t launch_chirp_in(const PassDesc& p, const float2* in, float2* A, hipStream_t s);
 hipError_t launch_chirp_rows(const PassDesc& p, float2* A, hipStream_t s);
 hipError_t launch_chirp_out(const PassDesc& p, const float2* A, float2* out, hipStream_t s);
+// Radix sequences of a streaming pass, and of the first and the second N-point
+// FFT of a convolution (of a long one's columns, or of its rows).
+std::vector<int> stream_radices(int L);
+std::vector<int> chirp_radices(int N, bool second);
 // Kernel names for tracing; step 0 .. 2 of a long axis.
 const char* chirp_kernel_name(const PassDesc& p, int step = 0);
 

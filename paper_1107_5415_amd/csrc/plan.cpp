@@ -20,6 +20,7 @@
 #include "fiber.hpp"
 #include "kernels.hpp"
 #include "ktrace.hpp"
+#include "roots.hpp"
 
 namespace lfft {
 
@@ -253,8 +254,8 @@ std::vector<int> pow2_radices(i64 n) {
 // Chirp-z tables of an axis or digit of length n: chirp[j] =
 // exp(-pi i (j^2 mod 2n) / n) for j < n, and the DFT of the convolution kernel
 // b (b_t = conj(chirp) at t and at N - t for 0 <= t < n, zero elsewhere) over
-// N points divided by N, in the order (k mod H, k / H); both built in FP64 and
-// rounded once.
+// N points divided by N and the FFTs' gain, in the order (k mod H, k / H); both
+// built in FP64 and rounded once.
 struct ChirpTables {
   const float2* chirp;
   const float2* bhat;
@@ -307,27 +308,72 @@ struct TwCache {
     std::vector<float2> cf(n), bf(N);
     for (i64 j = 0; j < n; ++j) cf[j] = make_float2((float)c[j].real(), (float)c[j].imag());
     const i64 R = N / H;
+    double div = (double)N;
+    for (bool second : {false, true}) {
+      div *= digit_gain(R, chirp_radices((int)R, second));
+      if (H > 1) div *= digit_gain(H, chirp_radices((int)H, second));
+    }
     for (i64 k = 0; k < N; ++k)
       bf[(k % H) * R + k / H] =
-          make_float2((float)(b[k].real() / (double)N), (float)(b[k].imag() / (double)N));
+          make_float2((float)(b[k].real() / div), (float)(b[k].imag() / div));
     ChirpTables t{blob->ref(cf), blob->ref(bf)};
     chirps[n] = t;
     return t;
   }
   std::map<i64, const float2*> full;
   std::map<i64, std::pair<const float2*, const float2*>> two;
+  std::map<i64, std::vector<double>> rounded;   // digits: Re(conj(w) fl(w)) - 1 of every entry
+  std::map<std::array<i64, 3>, double> stage_gains;
   const float2* table(i64 n) {
     auto it = full.find(n);
     if (it != full.end()) return it->second;
     std::vector<float2> t(n);
+    std::vector<double> d(n <= 2 * kMaxPencil ? n : 0);
     for (i64 k = 0; k < n; ++k) {
       // exact residue k/n; angle reduced by symmetry in double precision
       double a = -2.0 * M_PI * (double)k / (double)n;
-      t[k] = make_float2((float)std::cos(a), (float)std::sin(a));
+      const double c = std::cos(a), s = std::sin(a);
+      t[k] = make_float2((float)c, (float)s);
+      if (!d.empty()) d[k] = c * ((double)t[k].x - c) + s * ((double)t[k].y - s);
     }
+    if (!d.empty()) rounded[n].swap(d);
     const float2* p = blob->ref(t);
     full[n] = p;
     return p;
+  }
+  // Gain of one stage of radix R in a digit of length n (roots.hpp), its twiddles
+  // with it: those of the early stages are few, and a product of table entries
+  // has the gains of all of them.
+  double stage_gain(i64 n, i64 Ns, int R) {
+    auto at = stage_gains.find({{n, Ns, R}});
+    if (at != stage_gains.end()) return at->second;
+    double sum = 0;
+    if (Ns > 1) {
+      table(n);
+      const std::vector<double>& d = rounded[n];
+      const i64 step = n / (Ns * R);
+      for (i64 j = 0; j < Ns; ++j)
+        for (int i = 1; i < R; ++i) {
+          if (R > 16) {
+            sum += d[j * step * i];
+          } else {
+            for (int b = 1; b <= i; b *= 2)
+              if (i & b) sum += d[j * step * b];
+          }
+        }
+    }
+    const double g = dev::dft_gain(R) * (1.0 + sum / (double)(Ns * R));
+    stage_gains[{{n, Ns, R}}] = g;
+    return g;
+  }
+  double digit_gain(i64 n, const std::vector<int>& radices) {
+    double g = 1.0;
+    i64 Ns = 1;
+    for (int r : radices) {
+      g *= stage_gain(n, Ns, r);
+      Ns *= r;
+    }
+    return g;
   }
   std::pair<const float2*, const float2*> twolevel(i64 N) {
     auto it = two.find(N);
@@ -623,6 +669,22 @@ i64 batch_pencils(const LatticePlan* p, const PassDesc& pd) {
   return p->batch * (i64)pd.O * pd.S;
 }
 
+// What rounding its constants does to the length of the vectors of a pass.
+double pass_gain(const PassDesc& pd, TwCache& tw) {
+  if (pd.kind == 2) return tw.digit_gain(pd.L, stream_radices(pd.L));
+  if (pd.kind >= 3) return 1.0;   // split BF16: far below its error; chirp-z: in the kernel's DFT
+  double g = 1.0;
+  for (int i = 0; i < pd.nst; ++i) g *= tw.stage_gain(pd.st[i].n, pd.st[i].Ns, pd.st[i].radix);
+  return g;
+}
+
+// The output scale as a sum of two floats: rounded to one, it alone puts up to
+// 6e-8 on every value, half the error of a transform of 1000 points.
+void set_scale(PassDesc& pd, double f) {
+  pd.scale = (float)f;
+  pd.scale_lo = (float)(f - (double)pd.scale);
+}
+
 // Tile of a mixed-radix pass: up to 4096 elements (one pencil if it is
 // longer), fewer while that leaves less than three tiles per CU, but column
 // tiles keep 16 pencils (whole 128-byte segments) and short rows 256
@@ -664,6 +726,7 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
   const int np = (int)p->ranges.size();
   bool any_split = false;
   for (auto& g : dg) any_split |= (g.part != 0);
+  double gain = 1.0;
   for (int pi = 0; pi < np; ++pi) {
     const PassRange& R = p->ranges[pi];
     PassDesc pd{};
@@ -778,7 +841,8 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
       }
     }
     pd.sign = sign;
-    pd.scale = (pi == np - 1) ? (float)(1.0 / std::sqrt((double)p->m)) : 1.0f;
+    gain *= pass_gain(pd, tw);
+    set_scale(pd, pi == np - 1 ? 1.0 / (std::sqrt((double)p->m) * gain) : 1.0);
     pd.post = R.post ? 1 : 0;
     if (R.post) {
       // the high digit closes this pass (digit b - 1); the still untransformed
@@ -1079,7 +1143,7 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
       if (g.part == 3)
         p->chirp_ws = std::max(p->chirp_ws, (size_t)(batch * (p->m / g.n) * chirp_length(g.n)));
     p->ws_elems += p->chirp_ws;
-    TwCache tw{&p->blob, {}, {}, {}};
+    TwCache tw{&p->blob, {}, {}, {}, {}, {}};
     Side fs = sample_side(p->Sf, p->M);
     Side ff = freq_side(p->Sf, p->M);
     Mat MT = transpose(p->M);
@@ -1336,7 +1400,7 @@ void exec_lattice(const LatticePlan* p, bool inverse, bool in_grid, bool out_gri
     if (i == np - 1) {
       pd.out = out_grid ? E.out_grid : E.out_nat;
       pd.out.bstride = bout;
-      pd.scale *= scale_mul;
+      if (scale_mul != 1.0f) set_scale(pd, ((double)pd.scale + (double)pd.scale_lo) * scale_mul);
       if (out_grid) pd.stream_out = 0;
     }
     const double fft_bytes = 16.0 * (double)p->batch * (double)p->m;
@@ -1501,7 +1565,7 @@ WavePlan* build_wave_plan(int d, const i64* Mrm, const i64* Jrm, int levels, i64
         gcls.push_back(g);
       }
     }
-    TwCache tw{&w->blob, {}, {}, {}};
+    TwCache tw{&w->blob, {}, {}, {}, {}, {}};
     Mat Ml = w->M;
     for (int l = 0; l < levels; ++l) {
       WaveLevel L;
