@@ -1,6 +1,5 @@
 // In-register DFTs of any small length: odd primes by the symmetric sum over
-// x_j + x_{p-j} and x_j - x_{p-j}, composites as a product of two shorter
-// ones.  The roots of unity are compile-time constants, evaluated in FP64 and
+// x_j + x_{p-j} and x_j - x_{p-j}, composites by two shorter ones.  The roots of unity are compile-time constants, evaluated in FP64 and
 // rounded once.
 #pragma once
 #include "fft_common.hpp"
@@ -77,6 +76,30 @@ __device__ __forceinline__ void dft_two(float2* v, int sign) {
   }
 }
 
+// R = A B with A and B coprime: the inputs B n1 + A n2 and the outputs by their
+// residues modulo A and B make it a plain A x B transform, without twiddles
+// (Good's mapping), so with fewer products and roundings.
+template <int A, int B>
+__device__ __forceinline__ void dft_coprime(float2* v, int sign) {
+  constexpr int R = A * B;
+  float2 t[B][A];
+#pragma unroll
+  for (int n2 = 0; n2 < B; ++n2) {
+#pragma unroll
+    for (int n1 = 0; n1 < A; ++n1) t[n2][n1] = v[(B * n1 + A * n2) % R];
+    dft_small<A>(t[n2], sign);
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < A; ++k1) {
+    float2 u[B];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) u[n2] = t[n2][k1];
+    dft_small<B>(u, sign);
+#pragma unroll
+    for (int k = k1; k < R; k += A) v[k] = u[k % B];
+  }
+}
+
 template <int R>
 __device__ __forceinline__ void dft_small(float2* v, int sign) {
   if constexpr ((R & (R - 1)) == 0) {
@@ -84,17 +107,17 @@ __device__ __forceinline__ void dft_small(float2* v, int sign) {
   } else if constexpr (R == 3) {
     dft3(v, sign);
   } else if constexpr (R == 6) {
-    dft_two<2, 3>(v, sign);
+    dft_coprime<2, 3>(v, sign);
   } else if constexpr (R == 9) {
     dft_two<3, 3>(v, sign);
   } else if constexpr (R == 10) {
-    dft_two<2, 5>(v, sign);
+    dft_coprime<2, 5>(v, sign);
   } else if constexpr (R == 12) {
-    dft_two<4, 3>(v, sign);
+    dft_coprime<4, 3>(v, sign);
   } else if constexpr (R == 14) {
-    dft_two<2, 7>(v, sign);
+    dft_coprime<2, 7>(v, sign);
   } else if constexpr (R == 15) {
-    dft_two<3, 5>(v, sign);
+    dft_coprime<3, 5>(v, sign);
   } else {
     float2 y[R];
     dft_odd_emit<R>(v, sign, [&](int k, float2 x) { y[k] = x; });

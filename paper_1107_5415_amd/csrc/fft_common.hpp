@@ -126,6 +126,27 @@ __device__ __forceinline__ void dft_pow2(float2* v, int sign) {
   Combine<R, 0>::run(v, e, o, sign);
 }
 
+// Twiddles of a butterfly of radix R <= 16: input i is multiplied by w^i.
+// The powers 1 .. 3, 4, 8 and 12 (those below R) come from the table, the
+// others are one product of two of them (from w, w^2, w^4 and w^8 alone they
+// would be up to three in a row).
+constexpr int tw_bases(int R) { return R <= 4 ? R - 1 : R <= 8 ? 4 : R <= 12 ? 5 : 6; }
+constexpr int tw_exponent(int k) { return k < 4 ? k + 1 : 4 * (k - 2); }
+
+template <int R, int I = 1>
+__device__ __forceinline__ void apply_twiddles(float2* x, const float2* b) {
+  if constexpr (I < R) {
+    constexpr int lo = I & 3, hi = I >> 2;
+    if constexpr (hi == 0)
+      x[I] = c_mul(x[I], b[lo - 1]);
+    else if constexpr (lo == 0)
+      x[I] = c_mul(x[I], b[hi + 2]);
+    else
+      x[I] = c_mul(x[I], c_mul(b[hi + 2], b[lo - 1]));
+    apply_twiddles<R, I + 1>(x, b);
+  }
+}
+
 // v[i] <- v[(i - k) mod R], 0 <= k < R, different in every lane: a select per
 // value and bit of k, and no rounding.  In place, one cycle after the other.
 template <int R, int S = 1>

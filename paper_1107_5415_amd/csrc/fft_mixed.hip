@@ -60,30 +60,18 @@ __device__ __forceinline__ void split_bf(const PassDesc& p, FastDiv per, int npe
   }
 }
 
-// multiply input i by w^i, the powers built from w^(2^k) with at most
-// log2(R) products each (primes above 16: every power from the table)
-constexpr int high_bit(int i) { return i < 2 ? i : 2 * high_bit(i / 2); }
-
-template <int R, int I>
-__device__ __forceinline__ void power_products(float2* v, float2* pw) {
-  if constexpr (I < R) {
-    constexpr int hb = high_bit(I);
-    if constexpr (hb != I) pw[I] = c_mul(pw[hb], pw[I - hb]);
-    v[I] = c_mul(v[I], pw[I]);
-    power_products<R, I + 1>(v, pw);
-  }
-}
-
+// multiply input i by w^i (primes above 16: every power from the table)
 template <int R>
 __device__ __forceinline__ void apply_powers(float2* v, const float2* tw, unsigned e, int sign) {
   if constexpr (R > 16) {
 #pragma unroll
     for (int i = 1; i < R; ++i) v[i] = c_mul(v[i], tw_lookup(tw, (long long)(e * (unsigned)i), sign));
   } else {
-    float2 pw[R];
+    float2 b[tw_bases(R)];
 #pragma unroll
-    for (int i = 1; i < R; i *= 2) pw[i] = tw_lookup(tw, (long long)(e * (unsigned)i), sign);
-    power_products<R, 1>(v, pw);
+    for (int k = 0; k < tw_bases(R); ++k)
+      b[k] = tw_lookup(tw, (long long)(e * (unsigned)tw_exponent(k)), sign);
+    apply_twiddles<R>(v, b);
   }
 }
 

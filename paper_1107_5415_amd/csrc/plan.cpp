@@ -113,7 +113,9 @@ FastDiv make_fast_div(i64 d) {
 
 // Radices of the mixed-radix kernel for a digit of length n: the fewest
 // stages of radix 2 .. 16 or a prime (an LDS round trip and a barrier each),
-// then the smallest sum.  The first and the last stage of a pass load and
+// then the smallest sum, where 9 counts as 11.5: it is the one radix with
+// rotations in odd multiples (360 points as 9 8 5: 1.11e-7 from 64 bits, as
+// 10 6 6 1.07e-7).  The first and the last stage of a pass load and
 // store through the maps without a pass over LDS only up to radix 16, so a
 // prime above 16 stands at neither end where it can, and rather first (no
 // twiddles) than last.  first, last: the digit opens or closes the pencil.
@@ -129,14 +131,14 @@ std::vector<int> radices_of(i64 n, bool first, bool last) {
     while (rest % q == 0) rest /= q;
   }
   if (rest > 16) cand.push_back(rest);
-  // per divisor: stages, sum of the radices, the radix taken
+  // per divisor: stages, twice the sum of the radices, the radix taken
   std::vector<std::array<i64, 3>> best(divs.size(), {{1000, 0, 0}});
   best[0] = {{0, 0, 1}};
   for (size_t k = 1; k < divs.size(); ++k)
     for (i64 r : cand) {
       if (divs[k] % r != 0) continue;
       const size_t at = std::lower_bound(divs.begin(), divs.end(), divs[k] / r) - divs.begin();
-      const std::array<i64, 3> t{{best[at][0] + 1, best[at][1] + r, r}};
+      const std::array<i64, 3> t{{best[at][0] + 1, best[at][1] + (r == 9 ? 23 : 2 * r), r}};
       if (t < best[k]) best[k] = t;
     }
   std::vector<int> small, large, out;
@@ -343,9 +345,11 @@ struct TwCache {
   }
   // Gain of one stage of radix R in a digit of length n (roots.hpp), its twiddles
   // with it: those of the early stages are few, and a product of table entries
-  // has the gains of all of them.
-  double stage_gain(i64 n, i64 Ns, int R) {
-    auto at = stage_gains.find({{n, Ns, R}});
+  // (w^i by the bits of i, in the mixed-radix kernel w^(i & 3) w^(i & 12)) has
+  // the gains of all of them.
+  double stage_gain(i64 n, i64 Ns, int R, bool mixed = false) {
+    const std::array<i64, 3> key{{n, Ns, mixed ? -R : R}};
+    auto at = stage_gains.find(key);
     if (at != stage_gains.end()) return at->second;
     double sum = 0;
     if (Ns > 1) {
@@ -356,6 +360,8 @@ struct TwCache {
         for (int i = 1; i < R; ++i) {
           if (R > 16) {
             sum += d[j * step * i];
+          } else if (mixed) {
+            sum += d[j * step * (i & 3)] + d[j * step * (i & 12)];
           } else {
             for (int b = 1; b <= i; b *= 2)
               if (i & b) sum += d[j * step * b];
@@ -363,7 +369,7 @@ struct TwCache {
         }
     }
     const double g = dev::dft_gain(R) * (1.0 + sum / (double)(Ns * R));
-    stage_gains[{{n, Ns, R}}] = g;
+    stage_gains[key] = g;
     return g;
   }
   double digit_gain(i64 n, const std::vector<int>& radices) {
@@ -674,7 +680,7 @@ double pass_gain(const PassDesc& pd, TwCache& tw) {
   if (pd.kind == 2) return tw.digit_gain(pd.L, stream_radices(pd.L));
   if (pd.kind >= 3) return 1.0;   // split BF16: far below its error; chirp-z: in the kernel's DFT
   double g = 1.0;
-  for (int i = 0; i < pd.nst; ++i) g *= tw.stage_gain(pd.st[i].n, pd.st[i].Ns, pd.st[i].radix);
+  for (int i = 0; i < pd.nst; ++i) g *= tw.stage_gain(pd.st[i].n, pd.st[i].Ns, pd.st[i].radix, pd.kind == 0);
   return g;
 }
 

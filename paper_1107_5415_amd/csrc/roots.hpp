@@ -70,12 +70,12 @@ inline double dft_gain(int R) {
     // even and odd inputs by half the radix, the odd ones' outputs rotated
     case 8: return rotations_gain(2, 4);
     case 16: return dft_gain(8) * rotations_gain(2, 8);
-    case 6: return dft_gain(3) * rotations_gain(2, 3);
+    case 6: return dft_gain(3);
     case 9: return dft_gain(3) * dft_gain(3) * rotations_gain(3, 3);
-    case 10: return dft_gain(5) * rotations_gain(2, 5);
-    case 12: return dft_gain(3) * rotations_gain(4, 3);
-    case 14: return dft_gain(7) * rotations_gain(2, 7);
-    case 15: return dft_gain(3) * dft_gain(5) * rotations_gain(3, 5);
+    case 10: return dft_gain(5);
+    case 12: return dft_gain(3);
+    case 14: return dft_gain(7);
+    case 15: return dft_gain(3) * dft_gain(5);
     default: break;
   }
   // a prime: every root but 1 stands R - 1 times in the matrix
