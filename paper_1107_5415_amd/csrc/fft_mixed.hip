@@ -1,8 +1,8 @@
 // Mixed-radix FFT pass for gfx950: any pencil length up to 8192.  One
 // workgroup owns a tile of TP pencils that moves between two LDS buffers, one
 // Stockham stage per move; radices 2 .. 16 and the primes 17 .. 31 run in
-// registers, larger primes (only inside pencils of several digits; the others are
-// chirp-z passes) as a sum shared by all threads.
+// registers, the primes to 61 as sums shared by all threads, and so do larger
+// ones inside pencils of several digits (the others are chirp-z passes).
 //
 // The first stage reads its butterflies straight from the input order and the
 // last one writes straight to the output order, through the planner's maps
@@ -150,6 +150,74 @@ __device__ __forceinline__ void stage(PassArg arg, int si, const TileOf& t,
   }
 }
 
+// A stage of a prime radix R, 37 .. kMaxDirect: the inputs with their
+// twiddles are folded in place into x_j + x_{R-j} (at j) and x_j - x_{R-j} (at
+// R - j), then one thread forms the outputs k and R - k from sums of (R - 1) / 2
+// products each, over the R roots in LDS.  Bound by the latency of those LDS
+// reads: 55 signals of 592 = 16 x 37 points take 19.9 us (15.7 as a
+// convolution, which is 1.9e-7 from 64 bits instead of 1.2e-7), 13 of 2368
+// points 19.8 (22.2).
+__device__ __forceinline__ void stage_prime(PassArg arg, int si, const TileOf& t, float2* A,
+                                            float2* B, float2* roots) {
+  const PassDesc& p = fresh(arg);
+  const StageDesc& st = p.st[si];
+  const int R = st.radix, n = st.n, stride = st.stride, Ns = st.Ns;
+  const int nr = n / R, h = (R - 1) / 2, per = p.L / R;
+  const float2* tw = dev_ptr(st.tw);
+  for (int k = threadIdx.x; k < R; k += blockDim.x) roots[k] = tw[k * nr];
+  // butterfly bf: first input, twiddle exponent, first output; steps in0s, out0s
+  auto place = [&](unsigned bf, int& in0, int& e, int& out0) {
+    const int w = (int)fast_div(bf, st.f_per);
+    const unsigned q = bf - (unsigned)w * (unsigned)per;
+    const unsigned a = fast_div(q, st.f_stride), l_lo = q - a * (unsigned)stride;
+    const unsigned l_hi = fast_div(a, st.f_nr), j = a - l_hi * (unsigned)nr;
+    const unsigned jd = fast_div(j, st.f_Ns), jm = j - jd * (unsigned)Ns;
+    const int base = (int)(l_hi * (unsigned)(n * stride) + l_lo);
+    in0 = (base + (int)j * stride) * p.ls + w * p.ws;
+    e = n / (Ns * R) * (int)jm;
+    out0 = (base + (int)(jd * (unsigned)(Ns * R) + jm) * stride) * p.ls + w * p.ws;
+  };
+  const int in_step = nr * stride * p.ls, out_step = Ns * stride * p.ls;
+  const unsigned bfs = (unsigned)(t.n * per);
+  for (unsigned x = threadIdx.x; x < bfs * (unsigned)h; x += blockDim.x) {
+    const unsigned bf = x / (unsigned)h;
+    const int j = (int)(x - bf * (unsigned)h) + 1;
+    int in0, e, out0;
+    place(bf, in0, e, out0);
+    const int pa = mphys(in0 + j * in_step), pb = mphys(in0 + (R - j) * in_step);
+    float2 a = A[pa], b = A[pb];
+    if (Ns > 1) {
+      a = c_mul(a, tw_lookup(tw, e * j, p.sign));
+      b = c_mul(b, tw_lookup(tw, e * (R - j), p.sign));
+    }
+    A[pa] = c_add(a, b);
+    A[pb] = c_sub(a, b);
+  }
+  __syncthreads();
+  for (unsigned x = threadIdx.x; x < bfs * (unsigned)(h + 1); x += blockDim.x) {
+    const unsigned bf = x / (unsigned)(h + 1);
+    const int k = (int)(x - bf * (unsigned)(h + 1));
+    int in0, e, out0;
+    place(bf, in0, e, out0);
+    float2 a = A[mphys(in0)], b = make_float2(0.f, 0.f);
+    int r = 0;
+#pragma unroll 4
+    for (int j = 1; j <= h; ++j) {
+      r += k;
+      r -= r >= R ? R : 0;
+      const float2 w = roots[r];      // cos, -sin
+      const float2 s = A[mphys(in0 + j * in_step)], d = A[mphys(in0 + (R - j) * in_step)];
+      a.x += w.x * s.x;
+      a.y += w.x * s.y;
+      b.x -= w.y * d.x;
+      b.y -= w.y * d.y;
+    }
+    b = c_muli(b, p.sign);
+    B[mphys(out0 + k * out_step)] = c_add(a, b);
+    if (k) B[mphys(out0 + (R - k) * out_step)] = c_sub(a, b);
+  }
+}
+
 // A stage of any radix: one thread per output, the inputs from LDS (lanes of
 // one butterfly read the same word), the root's exponent kept by addition.
 __device__ __forceinline__ void stage_sum(PassArg arg, int si, const TileOf& t,
@@ -257,7 +325,12 @@ __global__ void __launch_bounds__(kPassThreads)
         LFFT_SMALL_RADIX(X)
         LFFT_MIXED_PRIME(X)
 #undef X
-        default: stage_sum(arg, si, t, A, B); break;
+        default:
+          if (radix <= kMaxDirect)
+            stage_prime(arg, si, t, A, B, lds + 2 * half);
+          else
+            stage_sum(arg, si, t, A, B);
+          break;
       }
     }
     __syncthreads();
@@ -293,7 +366,9 @@ hipError_t launch_mixed_t(const PassDesc& p, const float2* in, float2* out, hipS
   const long long npen = p.batch * (long long)p.O * p.S;
   const long long tiles = (npen + p.TP - 1) / p.TP;
   const int span = p.ls == 1 ? p.TP * p.ws : p.L * p.ls;
-  const size_t lds = (size_t)2 * (span + span / 16 + 1) * sizeof(float2);
+  bool prime = false;
+  for (int i = 0; i < p.nst; ++i) prime = prime || p.st[i].radix > 31;
+  const size_t lds = (size_t)(2 * (span + span / 16 + 1) + (prime ? kMaxDirect : 0)) * sizeof(float2);
   if (tiles <= 0) return hipSuccess;
   if (tiles > 0x7fffffffLL || lds > 160 * 1024 || p.NT < 64 || p.NT > kPassThreads)
     return hipErrorInvalidValue;

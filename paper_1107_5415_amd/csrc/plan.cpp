@@ -164,11 +164,22 @@ i64 chirp_length(i64 n) {
   return N;
 }
 
-// a prime factor too large for a register butterfly
+// A digit that is done as a convolution: it has a prime factor above kMaxDirect
+// or is itself a prime above the register radices.  The two transforms of a
+// convolution are of two to four times its length: 1845 = 45 x 41 points are
+// 1.84e-7 from 64 bits that way, 1.36e-7 with the 41 as a direct sum among
+// shorter stages.  Lengths with a prime above 61 are closer to 64 bits as
+// convolutions than the plain sum over that prime was (67: 1.6e-7, 127:
+// 2.1e-7), and faster.
 bool large_prime(i64 n) {
-  for (i64 q = 2; q <= 31; ++q)
-    while (n % q == 0) n /= q;
-  return n > 1;
+  i64 rest = n;
+  for (i64 q = 2; q <= kMaxDirect; ++q)
+    while (rest % q == 0) rest /= q;
+  if (rest > 1) return true;
+  if (n <= 31) return false;
+  for (i64 q = 2; q * q <= n; ++q)
+    if (n % q == 0) return false;
+  return true;
 }
 
 // Two on-chip digits n = hi * lo of at most kMaxPencil points each, 0 if
