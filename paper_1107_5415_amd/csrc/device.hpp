@@ -47,7 +47,8 @@ struct MapDesc {
   const int4* Ts;
   // register-resident kernel, last pass over rows: chain[t W + w] = (row,
   // position) of tile t's w-th row and of the w-th of W consecutive natural
-  // elements, the first of which lies at position 0 of the tile's first row;
+  // elements, the first of which lies at position 0 of the tile's first row (or
+  // of several shorter runs);
   // streaming and register-resident kernels, last pass over columns:
   // chain[w] = (column, position) likewise inside every tile of W columns, in
   // runs, and on the input side of a first pass over columns (NULL: in order)

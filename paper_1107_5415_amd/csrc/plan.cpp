@@ -520,8 +520,10 @@ MapDesc identity_map(bool across) {
 // Rows of the last pass (digits [0, a) x one digit of length n) in chains of
 // W natural neighbours, see MapDesc::chain: the step to the next natural
 // index moves row and position by fixed amounts, so the rows fall into cycles
-// of one length, cut into chains of W.  Empty if that step stays in its row
-// or the cycles are shorter than W.
+// of one length, cut into chains of W; shorter cycles share a tile, in runs of
+// their length ([[2048, 2], [0, 2048]], cycles of two: 67.3 us in plain order,
+// 59.9 so, 65.7 in single rows of 8192; four such signals 352, 267 and 326).
+// Empty if that step stays in its row or neither length divides the other.
 std::vector<int2> row_chains(const Side& side, const std::vector<i64>& eps,
                              const std::vector<Digit>& dg, int a, int W) {
   std::vector<int2> out;
@@ -550,7 +552,7 @@ std::vector<int2> row_chains(const Side& side, const std::vector<i64>& eps,
       for (size_t t = 0; t < eps.size(); ++t) mu[t] = (mu[t] + side.next[t]) % eps[t];
       pos = place(row);
     } while (row != first);
-    if (len < W || len % W != 0) return {};
+    if (len == 1 || (len < W ? W % len : len % W) != 0) return {};
   }
   return out;
 }
