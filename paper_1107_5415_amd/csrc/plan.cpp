@@ -737,6 +737,10 @@ void pass_divisions(const LatticePlan* p, PassDesc& pd) {
   pd.f_lon = make_fast_div(pd.post ? pd.lo_n : 1);
 }
 
+// Tiles of the register-resident kernel above 72 KB exchange real and imaginary
+// parts one after the other.
+int split_of(i64 elems) { return elems * 17 / 16 * 8 > 72 * 1024 ? 1 : 0; }
+
 void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& out_side, int sign,
                   TwCache& tw) {
   E.sign = sign;
@@ -753,6 +757,7 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
     pd.O = (int)range_count(dg, 0, R.a);
     pd.L = (int)range_count(dg, R.a, R.b);
     pd.S = (int)range_count(dg, R.b, D);
+    int grid_width = 0;   // columns of a tile from grid order, if others
     // register-resident kernel for power-of-two pencils of at least 32 points
     bool pow2 = pd.L >= 32 && pd.L <= kMaxPencil && (p->m < (i64(1) << 30));
     for (int g = R.a; g < R.b; ++g) pow2 = pow2 && is_pow2(dg[g].n);
@@ -791,16 +796,23 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
         // the input is larger than the L2s (32 MB).  Inverse of [[2048, k],
         // [0, 2048]], 8 / 16 columns: k = 8, 16, 32 76 / 67, 84 / 70, 87 / 79
         // us; in fewer tiles (k = 2) 57 / 63, with neighbours in one tile
-        // (forward, k = 8) 48.5 / 54, with 2 x 2^21 points 61 / 63.
+        // (forward, k = 8) 48.5 / 54, with 2 x 2^21 points 61 / 63, and from
+        // grid order, whose lines lie along the tile's rows, k = 8, 16, 32
+        // 45.9 / 50.5, 45.2 / 49.4, 47.5 / 54.8.
         const bool spread = np > 1 && pi == 0 && p->m >= (i64(1) << 22) &&
                             lines_apart(in_side, dg, R.a, R.b);
-        if (!spread) {
-          while (Wc > 8 && R.b - R.a > 1 && (i64)Wc * pd.L > 8192) Wc /= 2;
-        }
-        while (Wc > 8 && npen / Wc < (spread ? 256 : 512)) Wc /= 2;
+        auto width = [&](bool full) {
+          int w = Wc;
+          if (!full)
+            while (w > 8 && R.b - R.a > 1 && (i64)w * pd.L > 8192) w /= 2;
+          while (w > 8 && npen / w < (full ? 256 : 512)) w /= 2;
+          return w;
+        };
+        if (spread) grid_width = width(false);
+        Wc = width(spread);
         pd.W = Wc;
         pd.P = 16;
-        pd.split = ((i64)Wc * pd.L * 17 / 16 * 8 > 72 * 1024) ? 1 : 0;
+        pd.split = split_of(Wc * (i64)pd.L);
       }
       if ((i64)pd.W * pd.L / pd.P > 1024) pd.kind = 0;
       // the streaming kernel assumes full tiles inside one signal and
@@ -889,6 +901,12 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
     pd.in = identity_map(pd.S > 1);
     pd.out = identity_map(pd.S > 1);
     E.passes.push_back(pd);
+    if (pd.kind == 1 && grid_width != 0 && grid_width != pd.W) {
+      E.first_grid = pd;
+      E.first_grid.W = grid_width;
+      E.first_grid.split = split_of(grid_width * (i64)pd.L);
+      E.has_first_grid = true;
+    }
   }
   // map variants of the first and the last pass
   const PassRange& R0 = p->ranges.front();
@@ -941,20 +959,23 @@ void patch_map(MapDesc& m, uintptr_t base) {
   patch(m.chain, base);
 }
 
+void patch_pass(PassDesc& pd, uintptr_t base) {
+  for (int i = 0; i < pd.nst; ++i) patch(pd.st[i].tw, base);
+  patch(pd.tw_hi, base);
+  patch(pd.tw_lo, base);
+  patch(pd.chirp, base);
+  patch(pd.bhat, base);
+  patch(pd.tw_row, base);
+  patch(pd.tw_col, base);
+  patch(pd.cv_hi, base);
+  patch(pd.cv_lo, base);
+  patch_map(pd.in, base);
+  patch_map(pd.out, base);
+}
+
 void patch_engine(Engine& E, uintptr_t base) {
-  for (auto& pd : E.passes) {
-    for (int i = 0; i < pd.nst; ++i) patch(pd.st[i].tw, base);
-    patch(pd.tw_hi, base);
-    patch(pd.tw_lo, base);
-    patch(pd.chirp, base);
-    patch(pd.bhat, base);
-    patch(pd.tw_row, base);
-    patch(pd.tw_col, base);
-    patch(pd.cv_hi, base);
-    patch(pd.cv_lo, base);
-    patch_map(pd.in, base);
-    patch_map(pd.out, base);
-  }
+  for (auto& pd : E.passes) patch_pass(pd, base);
+  patch_pass(E.first_grid, base);
   patch_map(E.in_nat, base);
   patch_map(E.in_grid, base);
   patch_map(E.out_nat, base);
@@ -1048,10 +1069,15 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
           // kernels.  Not beyond the streaming kernels' 2^28 bound, where the
           // wider low digit measured faster overall.
           if (is_pow2(n) && n >= 32 * 32 && p->m < (i64(1) << 28)) {
-            // Rows of 8192 where those of 4096 would leave the high digit and
+              // Rows of 8192 where those of 4096 would leave the high digit and
             // the short axes before it 2048 points, eight to a tile, instead
-            // of 1024 in wider tiles: [[2048, 2], [0, 4096]] 151 / 116 us,
-            // inverse of [[4096, 32], [0, 2048]] 241 / 199.
+            // of 1024 in wider tiles.  One choice for all directions and
+            // layouts; us, rows of 8192 / 4096, k in [[2048, k], [0, 4096]]:
+            // forward k = 2, 4, 8, 16, 32 117 / 135, 109 / 111, 108 / 101,
+            // 105 / 100, 109 / 111; inverse 121 / 120, 140 / 134, 149 / 159,
+            // 153 / 180, 166 / 199 ([[4096, 8], [0, 2048]] 175 / 160, k = 16
+            // and 32 there 200 / 227, 198 / 240); inverse from grid order
+            // (8 columns) k = 4, 8, 16, 32 102 / 107, 101 / 96, 103 / 96, 105 / 105.
             i64 rows = p->m >= (i64(1) << 22) ? 4096 : 2048, lead = 1;
             for (auto& g : p->digits) lead *= g.n;
             if (rows == 4096 && lead > 1 && lead * (n / rows) == 2048 && n / 8192 >= 32) rows = 8192;
@@ -1406,7 +1432,7 @@ void exec_lattice(const LatticePlan* p, bool inverse, bool in_grid, bool out_gri
                              : (!nat ? p->inv_grid : (p->has_inv_rev ? p->inv_rev : p->inv_nat));
   const int np = (int)E.passes.size();
   for (int i = 0; i < np; ++i) {
-    PassDesc pd = E.passes[i];
+    PassDesc pd = i == 0 && in_grid && E.has_first_grid ? E.first_grid : E.passes[i];
     const float2* src = (i == 0) ? static_cast<const float2*>(in) : static_cast<const float2*>(ws);
     float2* dst = (i == np - 1) ? static_cast<float2*>(out) : static_cast<float2*>(ws);
     pd.in.bstride = p->m;

@@ -66,6 +66,8 @@ struct Engine {
   int sign = -1;
   std::vector<PassDesc> passes;
   MapDesc in_nat{}, in_grid{}, out_nat{}, out_grid{};
+  PassDesc first_grid{};    // the first pass from grid order, where its tiles differ
+  bool has_first_grid = false;
   bool has_nat_in = false, has_nat_out = false;
 };
 

@@ -1,7 +1,11 @@
 """Rows of a last pass whose natural neighbours come round after fewer rows than
-a tile holds, against the FP64 oracle.  Tolerance: 8 u per radix-2 level (u =
-2^-24: sums, products of twiddle powers and table rounding), 16 u for the
-four-step twiddle and the turn."""
+a tile holds, and grid layouts with tiles or a tile order of their own.
+
+Natural results are compared with the FP64 oracle, grid layouts with the
+natural transform of the same plan, which shares neither.  Tolerance: 8 u per
+radix-2 level (u = 2^-24: sums, products of twiddle powers and table rounding),
+16 u for the four-step twiddle and the turn; both sides of the second
+comparison may be that far off."""
 import math
 import os
 import subprocess
@@ -25,6 +29,8 @@ SHORT = [
     (((128, 4), (0, 128)), 2),
     (((64, 2), (0, 512)), 5),
 ]
+# first passes in tiles of 16 columns from natural order, of 8 from grid order
+GRID = [((2048, 8), (0, 4096)), ((4096, 32), (0, 2048))]
 
 
 def _rel(a, b):
@@ -60,3 +66,28 @@ def test_short_cycles_against_oracle(M, batch):
     assert _rel(plan.forward(xd).cpu().numpy(), dft.lattice_dft_hnf(M, z)) < _tol(m)
     back = dft.lattice_dft_hnf(M, z, inverse=True)
     assert _rel(plan.inverse(xd).cpu().numpy(), back) < _tol(m)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", GRID)
+def test_grid_layouts(M):
+    from paper_1107_5415_amd import lfft
+    m = abs(L.det(M))
+    print("case", M, flush=True)
+    plan = lfft.LatticePlan(M)
+    g = torch.Generator(device="cuda").manual_seed(206)
+    x = torch.randn(m, dtype=torch.complex64, device="cuda", generator=g)
+    s = torch.from_numpy(plan.index_map(lfft.LFFT_MAP_SAMPLES)).cuda()
+    f = torch.from_numpy(plan.index_map(lfft.LFFT_MAP_FREQS)).cuda()
+
+    def near(a, b):
+        d = torch.linalg.vector_norm((a - b).to(torch.complex128))
+        return (d / torch.linalg.vector_norm(b.to(torch.complex128))).item() < 2 * _tol(m)
+
+    for run, src, dst in ((plan.forward, s, f), (plan.inverse, f, s)):
+        natural = run(x)
+        xg = torch.empty_like(x)
+        xg[src] = x
+        assert near(run(xg, layout=lfft.LFFT_IN_GRID), natural)
+        assert near(run(x, layout=lfft.LFFT_OUT_GRID)[dst], natural)
+        assert near(run(xg, layout=lfft.LFFT_IN_GRID | lfft.LFFT_OUT_GRID)[dst], natural)
