@@ -53,6 +53,10 @@ struct MapDesc {
   // chain[w] = (column, position) likewise inside every tile of W columns, in
   // runs, and on the input side of a first pass over columns (NULL: in order)
   const int2* chain;
+  // LINEAR, streaming kernel, last pass over columns: the columns are groups x
+  // low indices of a four-step axis whose values lie side by side over the
+  // groups (0: no such axis)
+  int groups;
 };
 
 // One Stockham stage: radix r on the pass digit of length n whose stride

@@ -109,8 +109,10 @@ __device__ __forceinline__ void for_positions(const Addr<MODE>& A, const MapDesc
 #pragma unroll
     for (int i = 0; i < R; ++i) f(i, a + i * step * S);
   } else if constexpr (MODE == MAP_LINEAR) {
+    // (the positions differ in one digit)
+    const int a = A.lin + m.Tl[l0].x, da = m.Tl[step].x;
 #pragma unroll
-    for (int i = 0; i < R; ++i) f(i, A.lin + m.Tl[l0 + i * step].x);
+    for (int i = 0; i < R; ++i) f(i, a + i * da);
   } else {
     const int4 D = m.Tl[step];
     if (m.d == 2) {

@@ -922,6 +922,10 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
     m.To = p->blob.ref(linear_table(p->eps, dg, 0, R1.a));
     m.Tl = p->blob.ref(linear_table(p->eps, dg, R1.a, R1.b));
     m.Ts = p->blob.ref(linear_table(p->eps, dg, R1.b, D));
+    const PassDesc& end = E.passes.back();
+    if (end.kind == 2 && end.S > 1 && R1.b + 2 == D && dg[R1.b].part == 1 &&
+        dg[R1.b + 1].part == 2 && dg[R1.b + 1].n % end.W == 0)
+      m.groups = (int)dg[R1.b].n;
     E.out_grid = m;
   } else {
     E.out_grid = identity_map(E.passes.back().S > 1);

@@ -30,7 +30,8 @@ SHORT = [
     (((64, 2), (0, 512)), 5),
 ]
 # first passes in tiles of 16 columns from natural order, of 8 from grid order
-GRID = [((2048, 8), (0, 4096)), ((4096, 32), (0, 2048))]
+# and columns before a four-step axis in 32 groups of 16 tiles
+GRID = [((2048, 8), (0, 4096)), ((4096, 32), (0, 2048)), ((2048, 512), (0, 4096))]
 
 
 def _rel(a, b):
