@@ -26,6 +26,7 @@
 #include "fft_common.hpp"
 #include "kernels.hpp"
 #include "ktrace.hpp"
+#include "pass_addr.hpp"
 
 namespace lfft {
 namespace {
@@ -232,39 +233,48 @@ __device__ __forceinline__ long long side_index(const MapDesc& m, long long b, i
   }
 }
 
+// Tile element e -> (pencil w, position l): consecutive e are consecutive HBM
+// words of the identity layout on both pencil orientations (W and L are powers
+// of two).
+template <bool COLS>
+__device__ __forceinline__ void element(const PassDesc& p, int e, int& w, int& l) {
+  const int lg = COLS ? __builtin_ctz(p.W) : __builtin_ctz(p.L);
+  const int hi = e >> lg, lo = e & ((1 << lg) - 1);
+  w = COLS ? lo : hi;
+  l = COLS ? hi : lo;
+}
+
+// The pencil of every element by the planner's reciprocals and the descriptor
+// read in place: with 64-bit divisions and a copied descriptor, whose fields
+// spill as it grows, the transform of 256^3 points (sheared) took 657 us
+// forward and 702 back, 684 and 695 with a larger descriptor, 667 and 610 so;
+// 2^20 points 57 and 44.
 template <bool COLS, int MIN, int MOUT>
-__global__ void __launch_bounds__(kNT) fft_mfma_kernel(PassDesc p, const float2* __restrict__ in,
+__global__ void __launch_bounds__(kNT) fft_mfma_kernel(PassDesc, const float2* __restrict__ in,
                                                        float2* __restrict__ out) {
   extern __shared__ float2 lds[];
-  const int L = p.L, S = p.S, O = p.O, W = p.W;
+  const PassDesc& p = first_arg<PassDesc>();
+  const int L = p.L, S = p.S, W = p.W;
   const int tid = threadIdx.x;
-  const long long npen = p.batch * (long long)O * S;
-  const long long tile = xcd_tile(blockIdx.x, gridDim.x);
-  // load: element e -> (w, l); consecutive e are consecutive HBM words of
-  // the identity layout on both pencil orientations.  All loads are issued
-  // before the first LDS write, so their latencies overlap.
+  const TileOf t = tile_of_pencils(p, xcd_tile(blockIdx.x, gridDim.x) * W, W);
+  // load: all loads are issued before the first LDS write, so their latencies
+  // overlap
   {
     float2 v[kPer];
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      const int e = tid + kNT * k;
-      const int w = COLS ? e % W : e / L;
-      const int l = COLS ? e / W : e % L;
-      const long long pen = tile * W + w;
+      int w, l;
+      element<COLS>(p, tid + kNT * k, w, l);
       v[k] = make_float2(0.f, 0.f);
-      if (pen < npen) {
-        const long long bo = pen / S;
-        const int s = (int)(pen - bo * S);
-        const long long b = bo / O;
-        const int o = (int)(bo - b * O);
-        v[k] = in[side_index<MIN>(p.in, b, o, l, s, L, S)];
+      if (w < t.n) {
+        const Pencil c = pencil_of(p, t, w);
+        v[k] = in[side_index<MIN>(p.in, c.b, c.o, l, c.s, L, S)];
       }
     }
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      const int e = tid + kNT * k;
-      const int w = COLS ? e % W : e / L;
-      const int l = COLS ? e / W : e % L;
+      int w, l;
+      element<COLS>(p, tid + kNT * k, w, l);
       lds[phys(lds_pos<COLS>(l, w, W, L))] = v[k];
     }
   }
@@ -286,26 +296,17 @@ __global__ void __launch_bounds__(kNT) fft_mfma_kernel(PassDesc p, const float2*
     __syncthreads();
   }
   // store: four-step twiddle, 1/sqrt(m) scale, scatter
+  const float scale = p.scale, scale_lo = p.scale_lo;
+  const bool post = p.post != 0;
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int e = tid + kNT * k;
-    const int w = COLS ? e % W : e / L;
-    const int l = COLS ? e / W : e % L;
-    const long long pen = tile * W + w;
-    if (pen >= npen) continue;
-    const long long bo = pen / S;
-    const int s = (int)(pen - bo * S);
-    const long long b = bo / O;
-    const int o = (int)(bo - b * O);
+    int w, l;
+    element<COLS>(p, tid + kNT * k, w, l);
+    if (w >= t.n) continue;
+    const Pencil c = pencil_of(p, t, w);
     float2 x = lds[phys(lds_pos<COLS>(l, w, W, L))];
-    if (p.post) {
-      const long long lo = (s / p.lo_div) % p.lo_n;
-      const long long t = ((long long)(l % p.post_lmod) * lo) % p.postN;
-      float2 tw = c_mul(p.tw_hi[t >> 12], p.tw_lo[t & 4095]);
-      if (p.sign > 0) tw.y = -tw.y;
-      x = c_mul(x, tw);
-    }
-    out[side_index<MOUT>(p.out, b, o, l, s, L, S)] = c_scale(x, p.scale, p.scale_lo);
+    if (post) x = c_mul(x, post_twiddle(p, post_pos(p, (unsigned)l) * post_lo(p, c.s)));
+    out[side_index<MOUT>(p.out, c.b, c.o, l, c.s, L, S)] = c_scale(x, scale, scale_lo);
   }
 }
 
