@@ -1,8 +1,8 @@
 // Mixed-radix FFT pass for gfx950: any pencil length up to 8192.  One
 // workgroup owns a tile of TP pencils that moves between two LDS buffers, one
 // Stockham stage per move; radices 2 .. 16 and the primes 17 .. 31 run in
-// registers, the primes to 61 as sums shared by all threads, and so do larger
-// ones inside pencils of several digits (the others are chirp-z passes).
+// registers, larger primes as sums shared by all threads: a few of the longest
+// digits, and inside pencils of several digits (the others are chirp-z passes).
 //
 // The first stage reads its butterflies straight from the input order and the
 // last one writes straight to the output order, through the planner's maps
@@ -153,10 +153,8 @@ __device__ __forceinline__ void stage(PassArg arg, int si, const TileOf& t,
 // A stage of a prime radix R, 37 .. kMaxDirect: the inputs with their
 // twiddles are folded in place into x_j + x_{R-j} (at j) and x_j - x_{R-j} (at
 // R - j), then one thread forms the outputs k and R - k from sums of (R - 1) / 2
-// products each, over the R roots in LDS.  Bound by the latency of those LDS
-// reads: 55 signals of 592 = 16 x 37 points take 19.9 us (15.7 as a
-// convolution, which is 1.9e-7 from 64 bits instead of 1.2e-7), 13 of 2368
-// points 19.8 (22.2).
+// products each, over the R roots in LDS.  Bound by the vector ALUs of the few
+// CUs that such a pass fills: 13 signals of 2368 = 64 x 37 points take 19.8 us.
 __device__ __forceinline__ void stage_prime(PassArg arg, int si, const TileOf& t, float2* A,
                                             float2* B, float2* roots) {
   const PassDesc& p = fresh(arg);

@@ -88,8 +88,8 @@ hipError_t launch_unsplit_q_mask_grad(const SplitQDesc& sd, long long batch, con
                                       const float* mask, const float2* g, long long g_bs,
                                       float* gmask, hipStream_t s);
 
-// Primes up to this one are direct sums inside a longer digit.
-constexpr int kMaxDirect = 61;
+// Longest prime that the mixed-radix kernel sums in pairs of outputs.
+constexpr int kMaxDirect = 97;
 
 // Chirp-z on chip (kind 5): one launch.
 hipError_t launch_chirp_tile(const PassDesc& p, const float2* in, float2* out, hipStream_t s);

@@ -157,35 +157,53 @@ std::vector<int> radices_of(i64 n, bool first, bool last) {
 
 bool is_pow2(i64 n) { return n > 0 && (n & (n - 1)) == 0; }
 
-// smallest power of two of at least max(2n - 1, 128) points
+i64 largest_prime(i64 n) {
+  i64 p = 1;
+  for (i64 q = 2; q * q <= n; ++q)
+    while (n % q == 0) {
+      p = q;
+      n /= q;
+    }
+  return std::max(p, n);
+}
+
+// Relative errors (units of 1e-7) of n points as a convolution of N points and
+// with a plain sum over the largest prime p, fitted to 160 lengths each (within
+// 1% and 2.3%).  The convolution's rounding spreads over all N values, of which
+// u = (2n - 1) / N hold the result's energy n times over: a tight N is worse.
+double conv_error(i64 n, i64 N) {
+  const double u = (double)(2 * n - 1) / (double)N;
+  return std::sqrt(u * (0.323 * std::log2((double)N) - 0.875) + 0.634);
+}
+double sum_error(i64 n, i64 p) {
+  return std::sqrt(0.0322 * (double)p + 0.126 * std::log2((double)(n / p)) + 0.315);
+}
+
+// Smallest power of two of at least max(2n - 1, 128) points; the next one where
+// that is further from 64 bits than the sum over the largest prime (444 = 12 x
+// 37 points: 1.62e-7 in 1024 points, 1.38e-7 as a sum, 1.36e-7 in 2048, at the
+// same 16 us).  Not to 16384, which takes half as long again (22 -> 33 us).
 i64 chirp_length(i64 n) {
   i64 N = 128;
   while (N < 2 * n - 1) N *= 2;
+  if (N < kMaxPencil && conv_error(n, N) > sum_error(n, largest_prime(n))) N *= 2;
   return N;
 }
 
-// A digit that is done as a convolution: it has a prime factor above kMaxDirect
-// or is itself a prime above the register radices.  The two transforms of a
-// convolution are of two to four times its length: 1845 = 45 x 41 points are
-// 1.84e-7 from 64 bits that way, 1.36e-7 with the 41 as a direct sum among
-// shorter stages.  Lengths with a prime above 61 are closer to 64 bits as
-// convolutions than the plain sum over that prime was (67: 1.6e-7, 127:
-// 2.1e-7), and faster.
-bool large_prime(i64 n) {
-  i64 rest = n;
-  for (i64 q = 2; q <= kMaxDirect; ++q)
-    while (rest % q == 0) rest /= q;
-  if (rest > 1) return true;
-  if (n <= 31) return false;
-  for (i64 q = 2; q * q <= n; ++q)
-    if (n % q == 0) return false;
-  return true;
+// A digit that is done as a convolution: it has a prime factor above the
+// register radices, except where a convolution of 8192 or 16384 points is
+// further from 64 bits than the sum over a prime up to kMaxDirect (2368 = 64 x
+// 37 points: 1.59e-7, 1.53e-7 as a plain sum, 1.29e-7 by pairs).
+bool convolved(i64 n) {
+  const i64 p = largest_prime(n);
+  if (p <= 31) return false;
+  return n > kMaxPencil || p > kMaxDirect || conv_error(n, chirp_length(n)) <= sum_error(n, p);
 }
 
 // Two on-chip digits n = hi * lo of at most kMaxPencil points each, 0 if
 // there are none.  Powers of two: the longest lo.  Other cycles: the high
 // digit takes the whole axes before it (`lead` points) along if it can (no
-// pass over those axes alone), large primes go into as few and as short
+// pass over those axes alone), convolved digits are as few and as short
 // convolutions as possible (a chirp-z pass moves and transforms
 // chirp_length(L) / L values per point, and no other axis joins it), and then
 // the longer pencil is as short as possible (the tiles of the mixed-radix
@@ -197,11 +215,11 @@ i64 two_digit_lo(i64 n, i64 lead) {
     if (n % c != 0 || n / c > kMaxPencil) continue;
     if (is_pow2(n)) return c;
     const i64 hi = n / c;
-    const bool big = large_prime(hi);
+    const bool big = convolved(hi);
     const bool joint = lead == 1 || (!big && hi * lead <= kMaxPencil);
     double cost = joint ? 0.0 : 2.0;
     for (i64 L : {c, hi})
-      if (large_prime(L)) cost += 1.0 + 0.5 * (double)chirp_length(L) / (double)L;
+      if (convolved(L)) cost += 1.0 + 0.5 * (double)chirp_length(L) / (double)L;
     cost += (double)std::max(c, !big && joint ? hi * lead : hi) / (double)kMaxPencil;
     if (!best || cost < best_cost) {
       best = c;
@@ -825,7 +843,7 @@ void build_engine(LatticePlan* p, Engine& E, const Side& in_side, const Side& ou
     const bool one = R.b - R.a == 1;
     if (one && dg[R.a].part == 3)
       pd.kind = 4;   // a whole axis by chirp-z
-    else if (one && p->tile_lg == 0 && large_prime(pd.L) && p->m < (i64(1) << 30))
+    else if (one && p->tile_lg == 0 && convolved(pd.L) && p->m < (i64(1) << 30))
       pd.kind = 5;
     if (pd.kind >= 4) {
       // tables shared by every engine of the plan
@@ -1125,10 +1143,10 @@ LatticePlan* build_lattice_plan(int d, const i64* Mrm, i64 batch, uint32_t flags
     } else if (p->m <= kMaxTile) {
       p->ranges.push_back(PassRange{0, Dg, false, 0});
     } else {
-      // a digit with a large prime is a chirp-z pass of its own (below 2^30
+      // a convolved digit is a chirp-z pass of its own (below 2^30
       // points); others share passes up to one pencil
       auto alone = [&](int g) {
-        return p->m < (i64(1) << 30) && large_prime(p->digits[g].n);
+        return p->m < (i64(1) << 30) && convolved(p->digits[g].n);
       };
       auto joins = [&](int g, i64 prod) {   // digit g joins the pass of digit g + 1 ..
         return g >= 0 && p->digits[g].part == 0 && !alone(g) && prod * p->digits[g].n <= kMaxPencil;

@@ -81,7 +81,10 @@ FIGURES = [
     (((8209,),), 3, 2.626e-7, 2.645e-7),
     (((2, 0), (0, 2 * 8209)), 2, 2.297e-7, 2.284e-7),
     (((20, -196), (-367, 121)), 2, 2.701e-7, 2.695e-7),
-    # a prime of 37 .. 61 in a longer digit
+    # a prime of 37 .. 61 in a longer digit: sums, and tight convolutions
+    (((444,),), 100, 1.364e-7, 1.367e-7),
+    (((188,),), 200, 1.399e-7, 1.399e-7),
+    (((740,),), 60, 1.467e-7, 1.467e-7),
     (((2368,),), 50, 1.534e-7, 1.539e-7),
     (((1845,),), 50, 1.539e-7, 1.542e-7),
     (((3904,),), 30, 1.729e-7, 1.729e-7),
