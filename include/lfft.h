@@ -424,7 +424,10 @@ int lfft_batch_tune_clear(int* count);
 
 /* out = F(M_i) in (inverse != 0: F(M_i)^{-1}) for every lattice, in device
  * complex64 [sum m_i], out of place, on `stream`.  mode: LFFT_BATCH_*.
- * Calls on one plan must not overlap in time (they share the queue heads).
+ * Calls on one plan share no device state but the buffers given: on different
+ * streams they may overlap if workspaces and outputs differ.  The plan itself
+ * is not locked (graphs and single plans are built on first use): one host
+ * thread at a time.
  * Errors: ARG, STATE (host-only plan), HIP. */
 int lfft_batch_execute(lfft_batch_t plan, int inverse, int mode, const void* in, void* out,
                        void* workspace, hipStream_t stream);

@@ -1,6 +1,6 @@
 // Chirp-z (Bluestein) passes: the DFT of one grid axis, or of one four-step
-// digit of an axis, whose length L has a prime factor too large for a
-// register butterfly.  With w = exp(-2 pi i / L) and
+// digit of an axis, whose length L has a prime factor too large for a register
+// butterfly (a few such digits are direct sums, see the planner).  With w = exp(-2 pi i / L) and
 // jk = (j^2 + k^2 - (k - j)^2) / 2,
 //   X_k = sum_j x_j w^{jk} = c_k sum_j (x_j c_j) conj(c_{k-j}),  c_j = w^{j^2/2},
 // a cyclic convolution of length N >= 2L - 1 (a power of two).  The axis is

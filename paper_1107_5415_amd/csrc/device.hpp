@@ -79,7 +79,7 @@ struct PassDesc {
   int kind;                   // 0 mixed-radix, 1 register-resident power-of-two, 2 streaming,
                               // 3 split-BF16 MFMA, 4 chirp-z (a long axis),
                               // 5 chirp-z on chip (one digit of at most 8192 points)
-  int P;                      // fast kernel: points per thread (16 or 32)
+  int P;                      // fast kernel: points per thread (16)
   int W;                      // fast kernel: pencils per workgroup
   int split;                  // fast kernel: exchange real and imaginary parts separately
   long long batch;            // number of signals

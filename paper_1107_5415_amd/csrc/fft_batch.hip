@@ -4,7 +4,8 @@
 // fast_tile.hpp.  The tiles of all first passes (and of lattices done in one
 // pass) form phase 0, the tiles of all second passes phase 1; each phase is
 // one persistent launch over eight work queues, one per XCD, that the host
-// fills largest lattice first so that a lattice's tiles stay on one XCD.
+// fills largest lattice first, in runs of neighbouring tiles of one lattice
+// (1/128 of the phase), which share an L2.
 // The kernel boundary between the phases orders the two passes of every
 // lattice, so the tiles need no counters, fences or waits.
 //

@@ -63,25 +63,6 @@ __device__ __forceinline__ float2 root16(int k, int sign) {
   return make_float2(C[k], sign < 0 ? -Sn[k] : Sn[k]);
 }
 
-// exp(sign * 2 pi i k / 32) for k in [0, 16): cos and sin of multiples of pi/16
-__device__ __forceinline__ float2 root32(int k, int sign) {
-  constexpr float C[16] = {1.0f, 0.98078528040323044913f, 0.92387953251128675613f,
-                           0.83146961230254523708f, 0.70710678118654752440f,
-                           0.55557023301960222474f, 0.38268343236508977173f,
-                           0.19509032201612826785f, 0.0f, -0.19509032201612826785f,
-                           -0.38268343236508977173f, -0.55557023301960222474f,
-                           -0.70710678118654752440f, -0.83146961230254523708f,
-                           -0.92387953251128675613f, -0.98078528040323044913f};
-  constexpr float Sn[16] = {0.0f, 0.19509032201612826785f, 0.38268343236508977173f,
-                            0.55557023301960222474f, 0.70710678118654752440f,
-                            0.83146961230254523708f, 0.92387953251128675613f,
-                            0.98078528040323044913f, 1.0f, 0.98078528040323044913f,
-                            0.92387953251128675613f, 0.83146961230254523708f,
-                            0.70710678118654752440f, 0.55557023301960222474f,
-                            0.38268343236508977173f, 0.19509032201612826785f};
-  return make_float2(C[k], sign < 0 ? -Sn[k] : Sn[k]);
-}
-
 // o * exp(sign 2 pi i K / R) for a compile-time K < R / 2: the factors 1
 // and sign * i cost no multiplication (IEEE semantics keep the compiler
 // from dropping products with the constant 0 by itself).
@@ -91,8 +72,6 @@ __device__ __forceinline__ float2 rot_k(float2 o, int sign) {
     return o;
   } else if constexpr (4 * K == R) {
     return c_muli(o, sign);
-  } else if constexpr (R == 32) {
-    return c_mul(root32(K, sign), o);
   } else {
     return c_mul(root16(K * (16 / R), sign), o);
   }
@@ -113,7 +92,7 @@ struct Combine {
 
 template <int R>
 __device__ __forceinline__ void dft_pow2(float2* v, int sign) {
-  static_assert(R <= 32, "radix above 32");
+  static_assert(R <= 16, "radix above 16");
   // even/odd split: X[k] = E[k] + w^k O[k], X[k + R/2] = E[k] - w^k O[k]
   float2 e[R / 2], o[R / 2];
 #pragma unroll

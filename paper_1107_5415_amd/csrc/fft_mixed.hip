@@ -14,9 +14,10 @@
 // memory step.
 //
 // Bound by latency and by the vector ALUs, not by HBM: a stage is one LDS
-// round trip and a barrier, so stages are few and wide, and tiles are small
-// enough (4096 elements, 70 KB for both buffers) for two workgroups of eight
-// waves per CU.  All index splits are multiplications by precomputed
+// round trip and a barrier, so stages are few and wide, and tiles are small:
+// at most 4096 elements, 70 KB for both buffers and two workgroups of eight
+// waves per CU (columns of 2 or 3 points 104 KB with their padding, single
+// pencils near 8192 points 139 KB, one workgroup per CU).  All index splits are multiplications by precomputed
 // reciprocals: with the integer divisions (64-bit for every twiddle) of a
 // direct formulation, and single threads summing a prime's inputs, 1088
 // points (8 x 17) took 111 us and 8 x 135135 points 494 us; now 9 and 32 us

@@ -1812,7 +1812,8 @@ void build_channel_batches(WavePlan* w) {
   w->chan_batched.assign(w->levels, 0);
   for (int l = w->small_from; l < w->levels; ++l) {
     const WaveLevel& V = w->lv[l];
-    // (a long chirp-z axis needs more workspace than the staging leaves it)
+    // (channels with a long chirp-z axis are refused; below they would run
+    // level by level like the other lattices that are no powers of two)
     if (V.fftN->chirp_ws) throw StatusError{E_UNSUPPORTED};
     bool fits = V.ml / q >= 32 && V.ml / q <= (i64(1) << 26);
     for (i64 e : V.fftN->eps) fits = fits && is_pow2(e);
