@@ -109,10 +109,11 @@ __device__ __forceinline__ void for_positions(const Addr<MODE>& A, const MapDesc
 #pragma unroll
     for (int i = 0; i < R; ++i) f(i, a + i * step * S);
   } else if constexpr (MODE == MAP_LINEAR) {
-    // (the positions differ in one digit)
-    const int a = A.lin + m.Tl[l0].x, da = m.Tl[step].x;
+    // (an arithmetic progression, but with one constant in the place of the table
+    // reads the stores come in denser bursts over the same memory channels:
+    // [[4096, 1], [0, 4096]] into grid order 253 us, 238 so)
 #pragma unroll
-    for (int i = 0; i < R; ++i) f(i, a + i * da);
+    for (int i = 0; i < R; ++i) f(i, A.lin + m.Tl[l0 + i * step].x);
   } else {
     const int4 D = m.Tl[step];
     if (m.d == 2) {
